@@ -51,10 +51,11 @@ int check_config(const zo_config* c) {
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 // Workspace of zo_perturbed_losses_noalloc: a fixed device array, one copy per
-// device, held until the process ends. In host code `scratch` names a host
+// device, held until the process ends, half as large again as the account
+// (noalloc_account) that a call is held against. In host code `scratch` names a host
 // stand-in; its device address on the current device comes from
 // hipGetSymbolAddress, once per device, and only that address is ever used.
-constexpr size_t kScratchBytes = (size_t)ZO_NOALLOC_WORKSPACE_BYTES;
+constexpr size_t kScratchBytes = (size_t)ZO_NOALLOC_WORKSPACE_BYTES / 2 * 3 + (1u << 16);
 __device__ __align__(256) uint8_t scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -117,7 +118,7 @@ int zo_init(const zo_config* cfg, void* theta, uint64_t seed, void* stream) {
 static int forward_call(const zo_config* cfg, const void* theta, uint64_t seed, float eps, int32_t N,
                         uint32_t i0, const int32_t* tokens, const uint8_t* mask, int32_t B, int32_t C,
                         float* L1, float* L2, void* workspace, size_t ws_bytes, int32_t products,
-                        void* stream, bool fd, const char* name) {
+                        void* stream, bool fd, const char* name, bool regen = false) {
   zo::PhaseRange range(name);
   int st = check_config(cfg);
   if (st) return st;
@@ -143,8 +144,9 @@ static int forward_call(const zo_config* cfg, const void* theta, uint64_t seed, 
   const zo::Rows rows = zo::make_rows(N, B, zo::row_granule(*cfg, fd), fd);
   if (rows.M > (int64_t)1 << 30) return fail(ZO_ESHAPE, "rows of all passes too many");
   const zo::WsPlan plan = zo::plan_workspace(*cfg, rows, C);
-  if (ws_bytes < plan.min_total)
-    return fail(ZO_ENOMEM, "workspace of %zu bytes < %zu required", ws_bytes, plan.min_total);
+  // regen: the fixed scratch may lack room for the fp32 path's sign words
+  const size_t need = regen ? plan.regen_total : plan.min_total;
+  if (ws_bytes < need) return fail(ZO_ENOMEM, "workspace of %zu bytes < %zu required", ws_bytes, need);
   zo::ForwardArgs a;
   a.cfg = *cfg;
   a.lay = zo::make_layout(*cfg);
@@ -168,7 +170,11 @@ static int forward_call(const zo_config* cfg, const void* theta, uint64_t seed, 
     a.split = products == ZO_PRODUCTS_SPLIT;
   // the probe cache is used when the workspace has room for it
   a.zc = (zo::probe_cache_kind(*cfg) && ws_bytes >= plan.total) ? (char*)workspace + plan.zcache : nullptr;
-  a.bits = (zo::bit_cache_kind(*cfg) && ws_bytes >= plan.total) ? (uint32_t*)((char*)workspace + plan.bits) : nullptr;
+  // the sign words: always with fp32 weights (min_total holds them), with bf16
+  // weights when the workspace has room for them (total does)
+  a.bits = cfg->probe == ZO_RADEMACHER && ws_bytes >= (cfg->wdtype == ZO_WFP32 ? plan.min_total : plan.total)
+               ? (uint32_t*)((char*)workspace + plan.bits)
+               : nullptr;
   a.zmap = zo::make_zcache_map(*cfg);
   a.w16 = cfg->wdtype == ZO_WBF16 ? (char*)workspace + plan.w16 : nullptr;
   return device_status(zo::launch_forward(a, (hipStream_t)stream), name);
@@ -196,20 +202,20 @@ int zo_perturbed_losses_noalloc(const zo_config* cfg, const void* theta, uint64_
   if (st) return st;
   if (N < 1 || B < 1 || C < 1) return fail(ZO_EINVAL, "N, B and C must be >= 1");
   // the sizes are checked before the scratch array is first touched
-  const size_t need = zo_workspace_bytes_min(cfg, N, B, C);
-  if (need == 0) return fail(ZO_EINVAL, "invalid workspace request");
-  if (need > kScratchBytes)
+  if (!zo::config_valid(cfg)) return fail(ZO_EINVAL, "invalid workspace request");
+  const size_t need = std::max(zo::noalloc_account(*cfg, N, B, C, false), zo::noalloc_account(*cfg, N, B, C, true));
+  if (need > (size_t)ZO_NOALLOC_WORKSPACE_BYTES)
     return fail(ZO_ENOMEM, "zo_perturbed_losses_noalloc: %zu bytes of workspace needed, the fixed scratch holds %zu",
-                need, kScratchBytes);
+                need, (size_t)ZO_NOALLOC_WORKSPACE_BYTES);
   void* ws = nullptr;
   st = scratch_address(&ws);
   if (st) return st;
-  // the probe cache too when it fits (the results are the same either way)
-  const size_t full = zo_workspace_bytes(cfg, N, B, C);
-  const size_t bytes = full <= kScratchBytes ? full : need;
+  // the whole array: the probe cache and the sign words are used when they
+  // fit in it (the results are the same either way)
+  const size_t bytes = kScratchBytes;
   zo::g_profile_suppressed = true;
   st = forward_call(cfg, theta, seed, eps, N, i0, tokens, mask, B, C, Lplus, Lminus, ws, bytes, ZO_PRODUCTS_AUTO,
-                    stream, false, "zo_perturbed_losses_noalloc");
+                    stream, false, "zo_perturbed_losses_noalloc", true);
   zo::g_profile_suppressed = false;
   return st;
 }

@@ -3,6 +3,9 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stddef.h>
+
+#include <initializer_list>
+
 #include <stdint.h>
 
 #include "../../include/zo.h"
@@ -62,14 +65,16 @@ inline Layout make_layout(const zo_config& c) {
 //     for theta + eps z_n and 1 for theta - eps z_n;
 //   forward differences (N + 1 passes): row r = p Bp + b, pass p < N at
 //     theta + eps z_p, pass N at theta itself (the clean pass).
-constexpr int kRowGranuleF32 = 32;   // fp32 path: 64-row tiles, 32-row wave tiles
+constexpr int kRowGranuleF32 = 16;   // fp32 path: the row tile of its MFMAs and of the packed states
 constexpr int kRowGranuleBF16 = 128; // bf16 path: 256-row tiles
 
 inline int row_granule(const zo_config& c, bool fd = false) {
-  // forward differences: a whole row tile (64 or 256 rows) inside one pass
-  if (fd) return c.wdtype == ZO_WBF16 ? 2 * kRowGranuleBF16 : 2 * kRowGranuleF32;
-  return c.wdtype == ZO_WBF16 ? kRowGranuleBF16 : kRowGranuleF32;
+  if (c.wdtype != ZO_WBF16) return kRowGranuleF32;
+  // forward differences: a whole 256-row tile inside one pass
+  return fd ? 2 * kRowGranuleBF16 : kRowGranuleBF16;
 }
+// Bytes of one activation value: fp16 (bf16 weights), three bf16 parts (fp32 weights).
+inline size_t act_bytes(const zo_config& c) { return c.wdtype == ZO_WBF16 ? 2 : 6; }
 
 struct Rows {
   int32_t B, Bp, N;
@@ -113,7 +118,8 @@ __host__ __device__ inline PassOf pass_of(const RowMap& m, int64_t r) {
   return loc >= m.Bp ? PassOf{(int)p, -1, loc - m.Bp} : PassOf{(int)p, 1, loc};
 }
 
-// Time steps whose top-layer states are kept for one batched output-head pass.
+// Time steps whose top-layer states are kept for one batched output-head pass
+// (fp32 path: see time_chunk).
 constexpr int kTimeChunk = 16;
 
 // Output-head vocabulary tile (columns per workgroup): 256 on the bf16 path,
@@ -176,6 +182,9 @@ inline bool probe_cache_kind(const zo_config& c) { return c.probe == ZO_GAUSSIAN
 // the order in which the bf16 products turn a pair of flags into a packed
 // fp16 pair with one shift. The update can read the same words
 // (zo_update_cached) instead of regenerating them.
+// With fp32 weights every workspace holds the same words (fp32's share of a
+// probe is 32 times its bits), for the forward's own use; only the bf16 ones
+// are offered to callers.
 inline bool bit_cache_kind(const zo_config& c) { return c.probe == ZO_RADEMACHER && c.wdtype == ZO_WBF16; }
 __host__ __device__ inline uint64_t bit_words(uint64_t P) { return (P + 127) / 128 * 4; }
 
@@ -216,11 +225,12 @@ constexpr int kGaussCached = 2;
 constexpr int kSignsCached = 3;
 constexpr int kGaussPerturbed = 4;
 
-// Workspace plan (byte offsets from the workspace base, 256-aligned).
+// Workspace plan (byte offsets from the workspace base, 256-aligned). An
+// activation value takes act_bytes: fp16, or three bf16 parts (split_offset).
 struct WsPlan {
-  size_t x0;         // f32 [M][E]         perturbed embeddings of one timestep
-  size_t hbuf;       // f32 [L-1][2][M][H] double-buffered states of the lower layers
-  size_t hist;       // f32 [T][M][H]      top-layer states of the current time chunk
+  size_t x0;         // [M][E] perturbed embeddings of one timestep (bf16 path), [T][M][E] of a chunk (fp32)
+  size_t hbuf;       // [L-1][2][M][H]     double-buffered states of the lower layers
+  size_t hist;       // [T][M][H]          top-layer states of the current time chunk
   size_t cbuf;       // f32 [L][M][H]      cell states
   size_t zb;         // f32 [L][N][4H]     eps * z of the gate biases, per probe
   size_t zbo;        // f32 [N][V]         eps * z of the head bias, per probe
@@ -229,32 +239,43 @@ struct WsPlan {
   size_t ptgt;       // f32 [T*M]          target logit
   size_t row_loss;   // f64 [M]            masked loss sum of each row
   size_t w16;        // f16 [P_g]          bf16 weights: the product matrices in fp16 (ZCacheMap layout)
-  size_t min_total;  // bytes without the probe cache
+  size_t regen_total;  // bytes with which the forward can run at all (every probe regenerated in every tile)
+  size_t min_total;  // bytes the entry points ask for at least: as above, and the fp32 path's sign words
   size_t zcache;     // probe cache (normal probes; see ZCacheMap): fp32 weights [N][P_g] eps z;
                      // bf16 weights [N][2][P_g] fp16: probe n's perturbed weights
                      // fp16(w + fp16(eps z)) and fp16(w - fp16(eps z)) (fused products), or
                      // fp16(eps z) in the first N P_g values (two-stream products)
-  size_t bits;       // sign-probe cache [N][bit_words(P)] u32 (bf16 weights with sign probes)
+  size_t bits;       // sign words [N][bit_words(P)] u32 (sign probes)
   size_t total;      // bytes with the probe cache
   int nvt;           // vocabulary tiles
   int T;             // time chunk
 };
 
+// Time steps per chunk. bf16 path: kTimeChunk. fp32 path: as many (8 to 64) as
+// keep the chunk's buffers below 16 MiB: small models then take few head
+// launches, and the states of large ones stay near the caches.
+inline int time_chunk(const zo_config& c, int64_t M, int nvt, int32_t C) {
+  if (c.wdtype == ZO_WBF16) return C < kTimeChunk ? C : kTimeChunk;
+  const double step = (double)M * (((double)c.embed + c.hidden) * (double)act_bytes(c) + 8.0 * nvt + 4.0);
+  const double n = 16.0 * 1024 * 1024 / step;
+  const int T = n < 8 ? 8 : n > 64 ? 64 : (int)n;
+  return C < T ? C : T;
+}
+
 inline WsPlan plan_workspace(const zo_config& c, const Rows& r, int32_t C) {
   WsPlan w{};
   const size_t M = (size_t)r.M, E = (size_t)c.embed, H = (size_t)c.hidden, V = (size_t)c.vocab;
   const size_t L = (size_t)c.n_layers;
-  const size_t el = c.wdtype == ZO_WBF16 ? 2 : 4;  // activation operand element size
-  w.T = C < kTimeChunk ? C : kTimeChunk;
+  const size_t el = act_bytes(c);
   const size_t vt = (size_t)vocab_tile(c);
   w.nvt = (int)((V + vt - 1) / vt);
+  w.T = time_chunk(c, r.M, w.nvt, C);
   size_t p = 0;
   auto take = [&](size_t bytes) {
     size_t o = p;
     p = align_up(p + bytes, 256);
     return o;
   };
-  // perturbed embeddings: one timestep (bf16 path), a time chunk (fp32 path)
   w.x0 = take((c.wdtype == ZO_WBF16 ? 1 : (size_t)w.T) * M * E * el);
   w.hbuf = take((L - 1) * 2 * M * H * el);
   w.hist = take((size_t)w.T * M * H * el);
@@ -267,13 +288,37 @@ inline WsPlan plan_workspace(const zo_config& c, const Rows& r, int32_t C) {
   w.row_loss = take(M * 8);
   w.w16 = p;
   if (c.wdtype == ZO_WBF16) take((size_t)make_zcache_map(c).pg * 2);
+  w.regen_total = p;
+  const bool sign = c.probe == ZO_RADEMACHER;
+  const size_t bits = sign ? (size_t)r.N * bit_words(make_layout(c).total) * 4 : 0;
+  w.bits = p;
+  if (sign && c.wdtype == ZO_WFP32) take(bits);
   w.min_total = p;
   w.zcache = p;
   if (probe_cache_kind(c)) take((size_t)r.N * make_zcache_map(c).pg * (c.wdtype == ZO_WBF16 ? 2 * 2 : 4));
-  w.bits = p;
-  if (bit_cache_kind(c)) take((size_t)r.N * bit_words(make_layout(c).total) * 4);
+  if (bit_cache_kind(c)) {
+    w.bits = p;
+    take(bits);
+  }
   w.total = p;
   return w;
+}
+
+// What zo_perturbed_losses_noalloc holds against its fixed size. fp32 weights:
+// a fixed account of a call's needs (4 bytes per activation, chunks of
+// kTimeChunk, batches padded to 32 or 64 sequences), so that the shapes it
+// takes do not depend on how the forward lays out its buffers; a workspace
+// takes at most 1.5 times it.
+inline size_t noalloc_account(const zo_config& c, int32_t N, int32_t B, int32_t C, bool fd) {
+  if (c.wdtype == ZO_WBF16) return plan_workspace(c, make_rows(N, B, row_granule(c, fd), fd), C).min_total;
+  const size_t M = (size_t)make_rows(N, B, fd ? 64 : 32, fd).M, T = (size_t)(C < kTimeChunk ? C : kTimeChunk);
+  const size_t E = (size_t)c.embed, H = (size_t)c.hidden, V = (size_t)c.vocab, L = (size_t)c.n_layers;
+  const size_t nvt = (V + kVocabTile - 1) / kVocabTile;
+  size_t p = 0;
+  for (size_t bytes : {T * M * E * 4, (L - 1) * 2 * M * H * 4, T * M * H * 4, L * M * H * 4, L * (size_t)N * 4 * H * 4,
+                       (size_t)N * V * 4, nvt * T * M * 4, nvt * T * M * 4, T * M * 4, M * 8})
+    p = align_up(p + bytes, 256);
+  return p;
 }
 
 }  // namespace zo

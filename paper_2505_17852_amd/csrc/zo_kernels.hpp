@@ -45,11 +45,31 @@ struct ForwardArgs {
   bool split;       // two-stream products: A.W and A.(s eps z) as separate MFMA streams into one
                     // accumulator (bf16 weights: eps below the fused form's floor; fp32: measurement)
   void* zc;         // probe cache inside work, or nullptr (probes regenerated in every tile)
-  uint32_t* bits;   // sign-probe cache inside work (bf16 weights, sign probes), or nullptr
+  uint32_t* bits;   // sign-probe cache inside work (sign probes), or nullptr
   void* w16;        // bf16 weights: fp16 copy of the product matrices inside work (ZCacheMap layout)
   ZCacheMap zmap;
 };
 hipError_t launch_forward(const ForwardArgs& a, hipStream_t s);
+
+// k_forward_f32.hip: the fp32 path's kernels. Activations (x0, the states) are
+// split into three bf16 parts and packed (split_offset).
+hipError_t launch_embed_f32(const ForwardArgs& a, int t0, int Tc, void* x0, hipStream_t st);
+// One gate launch over n (<= kLaunchLayers) layer-timesteps.
+constexpr int kLaunchLayers = 8;
+struct GateLayerF32 {
+  const char* x;      // [M][El]
+  const char* hprev;  // [M][H]
+  char* hout;         // [M][H]
+  float* cst;         // [M][H] fp32, row-major
+  uint64_t off_ih, off_hh, off_b;
+  int El;
+  const float* zb;     // [N][4H] eps z of this layer's bias
+  const float* zc_ih;  // probe cache: W_ih's and W_hh's values of probe 0; probe n at + n * zc_stride
+  const float* zc_hh;
+};
+hipError_t launch_gates_f32(const ForwardArgs& a, const GateLayerF32* ls, int n, hipStream_t st);
+hipError_t launch_head_f32(const ForwardArgs& a, const void* hist, int t0, int Tc, const float* zbo,
+                           float* pmax, float* psum, float* ptgt, hipStream_t st);
 
 // k_forward_bf16.hip: the bf16 path's per-timestep kernels.
 hipError_t launch_embed_bf16(const ForwardArgs& a, int t, void* x0, hipStream_t st);

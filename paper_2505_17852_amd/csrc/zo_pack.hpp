@@ -109,4 +109,15 @@ __host__ __device__ inline uint32_t head_bias_bytes(uint32_t lead, int64_t V) {
   return (lead + 2u * (uint32_t)V + 3u) & ~3u;
 }
 
+// fp32 path: activations split into three bf16 parts and packed in the order
+// the v_mfma_f32_16x16x32_bf16 operands are read: part p of 16-row tile rt and
+// 32-k tile kt of a state with K values per row (a multiple of 32) is 1 KB at
+// ((rt (K / 32) + kt) 3 + p) 1024, lane L = row + 16 (k % 32) / 8 holding the 8
+// values k % 8. Byte offset of part 0 of element k of row `row` of tile rt (parts 1 and
+// 2 are 1024 and 2048 bytes further).
+constexpr int kSplitParts = 3;
+__host__ __device__ inline size_t split_offset(int64_t rt, int row, int k, int K) {
+  return (size_t)(rt * (K >> 5) + (k >> 5)) * (kSplitParts * 1024) + (size_t)((row + 16 * ((k & 31) >> 3)) * 16 + (k & 7) * 2);
+}
+
 }  // namespace zo

@@ -33,20 +33,48 @@ namespace {
 typedef float f4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
-// Bias probes: zb[l][n][c] = eps z_{i0+n}[bias_l + c], zbo[n][v] = eps z[b_out + v]
-// (the biases' perturbation is the same for every timestep).
+// What a call writes before its first timestep, in one launch (each launch of
+// a small model costs more than its work). First the zeros: every pass starts
+// from h = c = 0 and empty row sums (the state slots that timestep 0 reads, the
+// cell states, the row sums), n16 16-byte words per range; a kernel rather
+// than a memset, so that a caller can capture the forward into a graph and
+// replay it. Then the bias probes (the biases' perturbation is the same for
+// every timestep): zb[l][n][c] = eps z_{i0+n}[bias_l + c], zbo[n][v] = eps
+// z_{i0+n}[b_out + v].
+struct ZeroRanges {
+  uint4* slots;  // `n_slots` state slots of n_state words, `stride` words apart
+  int64_t n_slots, n_state, stride;
+  uint4* p[3];   // three more ranges
+  int64_t n[3];
+};
 struct BiasOffsets {
   uint64_t layer[kMaxLayers];
 };
 
-__global__ __launch_bounds__(256) void prep_bias_kernel(int kind, Key key, uint32_t i0, float eps,
-                                                        int N, int L, int H4, int V,
-                                                        BiasOffsets bias_off, uint64_t bout_off,
-                                                        float* zb, float* zbo) {
-  const int64_t per_layer = (int64_t)N * H4;
-  const int64_t total = per_layer * L + (int64_t)N * V;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-       t += (int64_t)gridDim.x * blockDim.x) {
+__global__ __launch_bounds__(256) void prepare_kernel(ZeroRanges zr, int kind, Key key, uint32_t i0, float eps, int N,
+                                                      int L, int H4, int V, BiasOffsets bias_off, uint64_t bout_off,
+                                                      float* zb, float* zbo) {
+  const int64_t per_layer = (int64_t)N * H4, biases = per_layer * L + (int64_t)N * V;
+  const int64_t slots = zr.n_slots * zr.n_state;
+  const int64_t zeros = slots + zr.n[0] + zr.n[1] + zr.n[2];
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < zeros + biases; i += (int64_t)gridDim.x * 256) {
+    if (i < zeros) {
+      uint4* q;
+      int64_t j = i - slots;
+      if (j < 0) {
+        const int64_t k = i / zr.n_state;
+        q = zr.slots + k * zr.stride + (i - k * zr.n_state);
+      } else if (j < zr.n[0]) {
+        q = zr.p[0] + j;
+      } else if ((j -= zr.n[0]) < zr.n[1]) {
+        q = zr.p[1] + j;
+      } else {
+        q = zr.p[2] + (j - zr.n[1]);
+      }
+      *q = uint4{0u, 0u, 0u, 0u};
+      continue;
+    }
+    const int64_t t = i - zeros;
     if (t < per_layer * L) {
       const int l = (int)(t / per_layer);
       const int64_t rem = t - l * per_layer;
@@ -65,105 +93,100 @@ __global__ __launch_bounds__(256) void prep_bias_kernel(int kind, Key key, uint3
 // ---------------------------------------------------------------------------
 // Cross-entropy of every position of the chunk: logsumexp over the
 // vocabulary tiles' (max, sum of exp) partials, merged online in tile order,
-// minus the target logit. One thread per (timestep, row); the loss replaces
-// the target logit in ptgt (0 for unscored positions and padding rows, NaN
-// for a scored position whose target token lies outside [0, V)).
-__global__ __launch_bounds__(256) void combine_kernel(const float* pmax, const float* psum,
-                                                      float* ptgt, int nvt, int64_t rows,
-                                                      int64_t M, int t0, int C, int B, RowMap rm,
-                                                      const uint8_t* mask, const int32_t* tokens, int V) {
-  const int64_t rr = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (rr >= rows) return;
-  const int tt = (int)(rr / M);
-  const int64_t r = rr - (int64_t)tt * M;
-  const int b = pass_of(rm, r).b;
-  if (b >= B || (mask && !mask[(int64_t)b * C + t0 + tt])) {
-    ptgt[rr] = 0.f;
-    return;
-  }
-  if ((uint32_t)tokens[(int64_t)b * (C + 1) + t0 + tt + 1] >= (uint32_t)V) {
-    ptgt[rr] = __builtin_nanf("");
-    return;
-  }
-  float mx = -INFINITY, s = 0.f;
-  for (int v = 0; v < nvt; ++v) {
-    const float m = pmax[(int64_t)v * rows + rr];
-    const float e = psum[(int64_t)v * rows + rr];
-    if (m == -INFINITY) continue;
-    if (m > mx) {
-      s = s * expf(mx - m) + e;
-      mx = m;
-    } else {
-      s += e * expf(m - mx);
+// minus the target logit (0 for unscored positions and padding rows, NaN for
+// a scored position whose target token lies outside [0, V)); then added to
+// each row's running sum in time order (a fixed summation order: the result
+// does not depend on scheduling). A workgroup takes 64 rows, thread (step,
+// row) one position of 16 timesteps at a time.
+constexpr int kCombineRows = 64, kCombineSteps = 16;
+__global__ __launch_bounds__(kCombineRows* kCombineSteps) void combine_kernel(
+    const float* pmax, const float* psum, const float* ptgt, int nvt, int64_t rows, int64_t M, int t0, int Tc, int C,
+    int B, RowMap rm, const uint8_t* mask, const int32_t* tokens, int V, double* row_loss) {
+  __shared__ float ell[kCombineSteps][kCombineRows];
+  const int lr = threadIdx.x % kCombineRows, step = threadIdx.x / kCombineRows;
+  const int64_t r = (int64_t)blockIdx.x * kCombineRows + lr;
+  const int b = r < M ? pass_of(rm, r).b : B;
+  double acc = step == 0 && r < M ? row_loss[r] : 0.0;
+  for (int c0 = 0; c0 < Tc; c0 += kCombineSteps) {
+    const int tt = c0 + step;
+    float loss = 0.f;
+    if (tt < Tc && b < B && !(mask && !mask[(int64_t)b * C + t0 + tt])) {
+      if ((uint32_t)tokens[(int64_t)b * (C + 1) + t0 + tt + 1] >= (uint32_t)V) {
+        loss = __builtin_nanf("");
+      } else {
+        const int64_t rr = (int64_t)tt * M + r;
+        float mx = -INFINITY, s = 0.f;
+        for (int v = 0; v < nvt; ++v) {
+          const float m = pmax[(int64_t)v * rows + rr];
+          const float e = psum[(int64_t)v * rows + rr];
+          if (m == -INFINITY) continue;
+          if (m > mx) {
+            s = s * expf(mx - m) + e;
+            mx = m;
+          } else {
+            s += e * expf(m - mx);
+          }
+        }
+        loss = mx + logf(s) - ptgt[rr];
+      }
     }
+    ell[step][lr] = loss;
+    __syncthreads();
+    if (step == 0)
+      for (int k = 0; k < kCombineSteps && c0 + k < Tc; ++k) acc += (double)ell[k][lr];
+    __syncthreads();
   }
-  ptgt[rr] = mx + logf(s) - ptgt[rr];
-}
-
-// Adds the chunk's per-position losses to each row's running sum, in time
-// order (a fixed summation order: the result does not depend on scheduling).
-__global__ __launch_bounds__(256) void accumulate_kernel(const float* ell, int64_t M, int Tc,
-                                                         double* row_loss) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= M) return;
-  double acc = row_loss[r];
-  for (int tt = 0; tt < Tc; ++tt) acc += (double)ell[(int64_t)tt * M + r];
-  row_loss[r] = acc;
+  if (step == 0 && r < M) row_loss[r] = acc;
 }
 
 // Loss of each pass = (sum over the pass's sequences of their row sums) /
 // (scored positions). Central differences: pass 2n -> Lp[n], 2n+1 -> Lm[n];
-// forward differences: pass p < N -> Lp[p], the clean pass N -> Lm[0].
+// forward differences: pass p < N -> Lp[p], the clean pass N -> Lm[0]. One
+// wave per pass; every workgroup counts the scored positions.
 __global__ __launch_bounds__(256) void reduce_kernel(const double* row_loss, int N, int B, int C,
                                                      RowMap rm, const uint8_t* mask, float* Lp,
                                                      float* Lm) {
-  __shared__ double part[256];
-  double cnt = 0.0;
+  __shared__ int64_t part[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t positions = (int64_t)B * C;
+  int64_t total = positions;
   if (mask) {
-    for (int64_t k = threadIdx.x; k < (int64_t)B * C; k += blockDim.x) cnt += mask[k] ? 1.0 : 0.0;
-  } else if (threadIdx.x == 0) {
-    cnt = (double)B * (double)C;
-  }
-  part[threadIdx.x] = cnt;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-    __syncthreads();
-  }
-  const double total = part[0];
-  const int npass = rm.fd ? N + 1 : 2 * N;
-  for (int p = threadIdx.x; p < npass; p += blockDim.x) {
-    double s = 0.0;
-    const double* rl = row_loss + (int64_t)p * rm.Bp;
-    for (int b = 0; b < B; ++b) s += rl[b];
-    const float L = total > 0.0 ? (float)(s / total) : 0.0f;
-    if (rm.fd) {
-      if (p < N) Lp[p] = L;
-      else Lm[0] = L;
-    } else if (p & 1) {
-      Lm[p >> 1] = L;
-    } else {
-      Lp[p >> 1] = L;
+    int64_t cnt = 0;
+    const int64_t whole = ((uintptr_t)mask & 15u) == 0 ? positions / 16 : 0;
+    for (int64_t k = threadIdx.x; k < whole; k += 256) {
+      const uint4 v = ((const uint4*)mask)[k];
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const uint32_t x = d == 0 ? v.x : d == 1 ? v.y : d == 2 ? v.z : v.w;
+        // bit 7 of each byte: the byte is not zero
+        cnt += __popc((x | ((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu)) & 0x80808080u);
+      }
     }
+    for (int64_t k = whole * 16 + threadIdx.x; k < positions; k += 256) cnt += mask[k] ? 1 : 0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, 64);
+    if (lane == 0) part[wave] = cnt;
+    __syncthreads();
+    total = part[0] + part[1] + part[2] + part[3];
   }
-}
-
-// Zero n16 16-byte words. A kernel rather than a memset, so that a caller can
-// capture the forward into a graph and replay it.
-__global__ __launch_bounds__(256) void zero_kernel(uint4* p, uint64_t n16) {
-  const uint64_t stride = (uint64_t)gridDim.x * 256u;
-  for (uint64_t i = (uint64_t)blockIdx.x * 256u + threadIdx.x; i < n16; i += stride) p[i] = uint4{0u, 0u, 0u, 0u};
-}
-
-// bytes: a multiple of 16 at a 16-byte aligned address (every workspace buffer is).
-hipError_t zero_async(void* p, size_t bytes, hipStream_t st) {
-  if (bytes == 0) return hipSuccess;
-  if ((bytes & 15u) || ((uintptr_t)p & 15u)) return hipErrorInvalidValue;
-  const uint64_t n16 = bytes / 16;
-  uint64_t grid = (n16 + 255) / 256;
-  if (grid > 8192) grid = 8192;
-  zero_kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>((uint4*)p, n16);
-  return hipGetLastError();
+  const int npass = rm.fd ? N + 1 : 2 * N;
+  const int p = (int)blockIdx.x * 4 + wave;
+  if (p >= npass) return;
+  double s = 0.0;
+  const double* rl = row_loss + (int64_t)p * rm.Bp;
+  for (int b = lane; b < B; b += 64) s += rl[b];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  if (lane != 0) return;
+  const float L = total > 0 ? (float)(s / (double)total) : 0.0f;
+  if (rm.fd) {
+    if (p < N) Lp[p] = L;
+    else Lm[0] = L;
+  } else if (p & 1) {
+    Lm[p >> 1] = L;
+  } else {
+    Lp[p >> 1] = L;
+  }
 }
 
 // Probe cache fill of the fp32 path: eps z of every weight matrix for probes
@@ -417,31 +440,32 @@ hipError_t launch_forward(const ForwardArgs& a, hipStream_t st) {
   const int T = W.T;
   std::optional<PhaseRange> phase;
   phase.emplace("forward: prepare");
-  // every pass starts from h = c = 0: zero what is read before it is written
-  // (the state slots that timestep 0 reads, the cell states) and the row sums
-  for (int l = 0; l + 1 < L; ++l) ZO_TRY(zero_async(hbuf + (size_t)(2 * l + 1) * state, state, st));
-  ZO_TRY(zero_async(hist + (size_t)(T - 1) * state, state, st));
-  ZO_TRY(zero_async(cbuf, (size_t)L * M * H * 4, st));
-  ZO_TRY(zero_async(row_loss, (size_t)M * 8, st));
+  {
+    ZeroRanges zr{};
+    zr.slots = (uint4*)(hbuf + state);  // slot 1 of every lower layer
+    zr.n_slots = L - 1;
+    zr.n_state = (int64_t)(state / 16);
+    zr.stride = 2 * zr.n_state;
+    zr.p[0] = (uint4*)(hist + (size_t)(T - 1) * state);
+    zr.n[0] = zr.n_state;
+    zr.p[1] = (uint4*)cbuf;
+    zr.n[1] = (int64_t)((size_t)L * M * H / 4);
+    zr.p[2] = (uint4*)row_loss;
+    zr.n[2] = M / 2;
+    BiasOffsets boff{};
+    for (int l = 0; l < L; ++l) boff.layer[l] = a.lay.bias[l];
+    const int64_t total = zr.n_slots * zr.n_state + zr.n[0] + zr.n[1] + zr.n[2] + (int64_t)R.N * 4 * H * L + (int64_t)R.N * V;
+    const unsigned grid = (unsigned)std::min<int64_t>((total + 255) / 256, 65536);
+    prepare_kernel<<<dim3(grid), dim3(256), 0, st>>>(zr, c.probe, make_key(a.seed), a.i0, a.eps, R.N, L, 4 * H, V, boff,
+                                                     a.lay.b_out, zb, zbo);
+    ZO_TRY(hipGetLastError());
+  }
 
   // bf16 weights: the fp16 copy of the product matrices; probe cache (normal
   // probes, when the workspace holds it)
   if (bf16) ZO_TRY(launch_w16_fill(a, st));
   if (a.zc) ZO_TRY(launch_zcache_fill(a, st));
   if (a.bits) ZO_TRY(launch_bits_fill(a.bits, a.lay.total, a.seed, a.i0, R.N, st));
-
-  // bias probes
-  {
-    BiasOffsets boff{};
-    for (int l = 0; l < L; ++l) boff.layer[l] = a.lay.bias[l];
-    const int64_t total = (int64_t)R.N * 4 * H * L + (int64_t)R.N * V;
-    int64_t grid = (total + 255) / 256;
-    if (grid > 65536) grid = 65536;
-    prep_bias_kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>(c.probe, make_key(a.seed), a.i0,
-                                                                a.eps, R.N, L, 4 * H, V, boff,
-                                                                a.lay.b_out, zb, zbo);
-    ZO_TRY(hipGetLastError());
-  }
 
   // states of layer l at time t: lower layers alternate between two slots
   // (time t in slot t & 1), the top layer writes the time-chunk ring
@@ -506,16 +530,14 @@ hipError_t launch_forward(const ForwardArgs& a, hipStream_t st) {
       PhaseRange head_range("forward: head and cross entropy of a time chunk");
       ZO_TRY(head(a, hist, t0, Tc, zbo, pmax, psum, ptgt, st));
       ProfScope ps(kKCombine, st);
-      const int64_t rows = (int64_t)Tc * M;
-      combine_kernel<<<dim3((unsigned)((rows + 255) / 256)), 256, 0, st>>>(
-          pmax, psum, ptgt, W.nvt, rows, M, t0, a.C, R.B, rm, a.mask, a.tokens, a.cfg.vocab);
-      ZO_TRY(hipGetLastError());
-      accumulate_kernel<<<dim3((unsigned)((M + 255) / 256)), 256, 0, st>>>(ptgt, M, Tc, row_loss);
+      combine_kernel<<<dim3((unsigned)((M + kCombineRows - 1) / kCombineRows)), kCombineRows * kCombineSteps, 0, st>>>(
+          pmax, psum, ptgt, W.nvt, (int64_t)Tc * M, M, t0, Tc, a.C, R.B, rm, a.mask, a.tokens, a.cfg.vocab, row_loss);
       ZO_TRY(hipGetLastError());
     }
   }
   PhaseRange reduce_range("forward: loss reduction");
-  reduce_kernel<<<1, 256, 0, st>>>(row_loss, R.N, R.B, a.C, rm, a.mask, a.Lplus, a.Lminus);
+  const unsigned npass = R.fd ? (unsigned)R.N + 1u : 2u * (unsigned)R.N;
+  reduce_kernel<<<(npass + 3) / 4, 256, 0, st>>>(row_loss, R.N, R.B, a.C, rm, a.mask, a.Lplus, a.Lminus);
   ZO_TRY(hipGetLastError());
 #undef ZO_TRY
   return hipSuccess;

@@ -92,6 +92,14 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){lo, hi}, bf2));
 }
 
+// The magnitude bits m with a sign from bit 31 of x (set: plus), in one
+// instruction: (~x & 0x80000000) ^ m.
+__device__ __forceinline__ uint32_t sign_of(uint32_t x, uint32_t m) {
+  uint32_t d;
+  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xa6" : "=v"(d) : "v"(x), "s"(0x80000000u), "v"(m));
+  return d;
+}
+
 // (a, b) = sum of the three packed bf16 pairs p[0] + p[1] + p[2] (exact: 24
 // bits in three parts of 8; the lowest parts of values below 2^-109 flush).
 __device__ __forceinline__ void split3(float a, float b, uint32_t (&p)[3]) {
@@ -174,10 +182,10 @@ struct Shape {
   static constexpr bool kZ = kind == kGaussCached;  // cached eps z beside the weights
   static constexpr bool kBits = kind == kSignsCached;
   static constexpr int LPT = CT * (2 + (kZ ? 2 : kBits ? 1 : 0));  // register loads per k tile
-  static constexpr int Copies = (S * RT * 3 + 3) / 4;              // LDS copies per wave, stage and half of the rows
   static_assert(RT >= 1 && RT <= 4 && (CT == 1 || CT == 2), "shape");
   static_assert(S * RTT * kFrag <= kStageBytes, "stage");
   static_assert((2 * S) % NB == 0, "the weight buffers repeat every two stages");
+  static_assert(RT * S <= 4, "each wave copies one (row tile, k tile) of a half");
 };
 
 // The rows of a workgroup: up to RTT row tiles of 16 rows. Tiles past the end
@@ -189,30 +197,29 @@ struct RowTiles {
   int sign0, sign1;      // the sign of eps of each half's rows (+1, -1, 0)
 };
 template <int NS, int RT>
-__device__ __forceinline__ RowTiles row_tiles(const RowMap& rm, int64_t blk) {
+__device__ __forceinline__ RowTiles row_tiles(const RowMap& rm, int blk) {
   const int q = rm.Bp >> 4;
   RowTiles r;
   if constexpr (NS == 2) {
     const int nblk = (q + RT - 1) / RT;
-    const int64_t n = blk / nblk;
-    const int j = (int)(blk - n * nblk) * RT;
-    r.base0 = 2 * n * q + j;
+    const int n = blk / nblk;
+    const int j = (blk - n * nblk) * RT;
+    r.base0 = (int64_t)(2 * n) * q + j;
     r.base1 = r.base0 + q;
     r.last0 = r.last1 = min(RT, q - j) - 1;
-    r.probe = (int)n;
+    r.probe = n;
     r.sign0 = 1;
     r.sign1 = -1;
   } else {
     const int nblk = (q + 2 * RT - 1) / (2 * RT);
-    const int64_t p = blk / nblk;
-    const int j = (int)(blk - p * nblk) * 2 * RT;
-    r.base0 = p * q + j;
+    const int p = blk / nblk;
+    const int j = (blk - p * nblk) * 2 * RT;
+    r.base0 = (int64_t)p * q + j;
     r.base1 = r.base0 + RT;
     r.last0 = min(RT, q - j) - 1;
     r.last1 = min(RT, q - j - RT) - 1;  // may be negative: the second half repeats the last tile of the first
-    const PassOf ps = pass_of(rm, p * rm.Bp);
-    r.probe = ps.probe;
-    r.sign0 = r.sign1 = ps.sign;
+    r.probe = min(p, rm.N - 1);  // as pass_of: the clean pass reports the last probe with sign 0
+    r.sign0 = r.sign1 = p < rm.N ? 1 : 0;
   }
   return r;
 }
@@ -256,11 +263,11 @@ struct Seg {
 // rows 4 (lane / 16) + v. row0: the wave's first weight row (uniform); col(ct):
 // this lane's weight row of column tile ct, from row0. split: the two products W.h and (s eps z).h one after the other into
 // one accumulator (twice the matrix work, for measurement).
-template <typename T, bool kSplit, typename Col>
+template <typename T, bool kSplit, typename Col, typename Init>
 __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0, const Seg s1, int nseg,
                                          const RowTiles& rt, int row0, Col col, Key key, uint32_t probe, float eps,
-                                         const uint32_t* bits, uint8_t* st0, uint8_t* st1) {
-  constexpr int NS = T::NS, RT = T::RT, RTT = T::RTT, CT = T::CT, S = T::S, NB = T::NB, PD = T::PD;
+                                         const uint32_t* bits, uint8_t* st0, uint8_t* st1, Init init) {
+  constexpr int NS = T::NS, RT = T::RT, CT = T::CT, S = T::S, NB = T::NB, PD = T::PD;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kg = lane >> 4;
@@ -273,25 +280,33 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
     int g;
   };
   Buf buf[NB];
-  // lane part of the weights' offsets: this lane's row of column tile c and
-  // its 8 k, from the wave's first row (32 rows of K fp32 values at most)
+  // Addresses of the weights: per segment the wave's first row (uniform) and
+  // this lane's byte offset from it (its row of column tile c and its 8 k, 32
+  // rows of K fp32 values at most); the k tile adds 128 bytes. Sign words: 32
+  // values per 4-byte word (K is a multiple of 32).
   int rel[CT];
-  uint32_t lo[2][CT];
+  uint32_t lo[2][CT], lw[2][CT];
 #pragma unroll
   for (int c = 0; c < CT; ++c) {
     rel[c] = col(c);
     lo[0][c] = (uint32_t)(rel[c] * s0.K + 8 * kg) * 4u;
     lo[1][c] = (uint32_t)(rel[c] * s1.K + 8 * kg) * 4u;
+    lw[0][c] = (uint32_t)(rel[c] * (s0.K >> 5)) * 4u;
+    lw[1][c] = (uint32_t)(rel[c] * (s1.K >> 5)) * 4u;
   }
-
+  const int64_t r0 = (int64_t)row0 * s0.K, r1 = (int64_t)row0 * s1.K;
+  const char* wbase[2] = {(const char*)(s0.W + r0), (const char*)(s1.W + r1)};
+  const char* zbase[2] = {(const char*)(s0.Z + r0), (const char*)(s1.Z + r1)};
+  const char* bbase[2] = {(const char*)(bits + ((s0.zoff + (uint64_t)r0) >> 5)),
+                          (const char*)(bits + ((s1.zoff + (uint64_t)r1) >> 5))};
   // weights (and probe values or sign words) of k tile g, the last tile past the end
   auto load_b = [&](Buf& b, int g) {
     g = min(g, ntiles - 1);
     const bool second = g >= kt0;
-    const int64_t o = (int64_t)row0 * (second ? s1.K : s0.K) + (second ? g - kt0 : g) * 32;
-    const char* W = (const char*)((second ? s1.W : s0.W) + o);
-    const char* Z = (const char*)((second ? s1.Z : s0.Z) + o);
-    const char* wd = (const char*)(bits + (((second ? s1.zoff : s0.zoff) + (uint64_t)o) >> 5));
+    const uint32_t kt = (uint32_t)(second ? g - kt0 : g);
+    const char* W = (second ? wbase[1] : wbase[0]) + kt * 128u;
+    const char* Z = (second ? zbase[1] : zbase[0]) + kt * 128u;
+    const char* wd = (second ? bbase[1] : bbase[0]) + kt * 4u;
     b.g = g;
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
@@ -302,56 +317,51 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
         b.z[c][0] = *(const f4*)(Z + v);
         b.z[c][1] = *(const f4*)(Z + v + 16);
       }
-      // 32 values per 4-byte word: a thirty-second of the weights' offset, whole words (K is a multiple of 32)
-      if constexpr (T::kBits) b.word[c] = *(const uint32_t*)(wd + ((v >> 7) << 2));
+      if constexpr (T::kBits) b.word[c] = *(const uint32_t*)(wd + (second ? lw[1][c] : lw[0][c]));
     }
   };
-  // the activation tiles of stage s (S k tiles of every row tile) into st:
-  // fragment u of a half's S RT 3 goes with row tile u / (3 S), k tile
-  // (u / 3) % S, part u % 3. A half's row tiles follow one another in memory,
-  // so one resource per segment and half reaches them (offsets below RT K 96).
-  uint32_t cu[T::Copies], ck[T::Copies], co[2][2][T::Copies];  // fragment, k tile in the stage, offsets [segment][half]
-  const int64_t first[2] = {rt.base0 + min(0, rt.last0), rt.base1 + min(0, rt.last1)};
-  const int last[2] = {max(0, rt.last0), max(0, rt.last1)};
-#pragma unroll
-  for (int c = 0; c < T::Copies; ++c) {
-    const int u = min(4 * c + wave, S * RT * 3 - 1);
-    cu[c] = (uint32_t)u;
-    ck[c] = (uint32_t)(u / 3 % S);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t i = (uint32_t)min(u / (3 * S), last[h]), p = (uint32_t)(u % 3) * kPart;
-      co[0][h][c] = i * (uint32_t)kt0 * kFrag + p;
-      co[1][h][c] = i * (uint32_t)(s1.K >> 5) * kFrag + p;
-    }
-  }
+  // The activation tiles of stage s (S k tiles of every row tile) into st:
+  // wave w copies row tile w / S of each half and k tile w % S, part by part
+  // (the instruction's offset moves both the source and the LDS address). A
+  // half's row tiles follow one another in memory, so one resource per
+  // segment and half reaches them (offsets below RT K 96).
+  const int ck = wave % S;
   const char* abase[2][2];
+  uint32_t co[2][2];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    abase[0][h] = s0.A + first[h] * kt0 * kFrag;
-    abase[1][h] = s1.A + first[h] * (s1.K >> 5) * kFrag;
+    const int last = h ? rt.last1 : rt.last0;
+    const int64_t first = (h ? rt.base1 : rt.base0) + min(0, last);
+    const uint32_t i = (uint32_t)min(min(wave / S, RT - 1), max(0, last));
+    abase[0][h] = s0.A + first * kt0 * kFrag;
+    abase[1][h] = s1.A + first * (s1.K >> 5) * kFrag;
+    co[0][h] = i * (uint32_t)kt0 * kFrag;
+    co[1][h] = i * (uint32_t)(s1.K >> 5) * kFrag;
   }
   const uint32_t abytes[2] = {(uint32_t)(RT * kt0 * kFrag), (uint32_t)(RT * (s1.K >> 5) * kFrag)};
+  const int cdst = (min(wave / S, RT - 1) * S + ck) * kFrag;
   auto copy_a = [&](uint8_t* st, int s) {
+    const int g = min(s * S + ck, ntiles - 1);
+    const bool second = g >= kt0;
+    const uint32_t kt = (uint32_t)(second ? g - kt0 : g) * kFrag;
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int c = 0; c < T::Copies; ++c) {
-        const int g = min(s * S + (int)ck[c], ntiles - 1);
-        const bool second = g >= kt0;
-        const Rsrc r = make_rsrc(second ? abase[1][h] : abase[0][h], second ? abytes[1] : abytes[0]);
-        const uint32_t off = (second ? co[1][h][c] : co[0][h][c]) + (uint32_t)(second ? g - kt0 : g) * kFrag;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            r, (__attribute__((address_space(3))) void*)(st + (h * S * RT * 3 + cu[c]) * kPart), 16, lane * 16, off, 0, 0);
-      }
+    for (int h = 0; h < 2; ++h) {
+      const Rsrc r = make_rsrc(second ? abase[1][h] : abase[0][h], second ? abytes[1] : abytes[0]);
+      const uint32_t off = (second ? co[1][h] : co[0][h]) + kt;
+      auto* dst = (__attribute__((address_space(3))) void*)(st + h * RT * S * kFrag + cdst);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, lane * 16, off, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, lane * 16, off, kPart, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, lane * 16, off, 2 * kPart, 0);
+    }
   };
 
+  const uint32_t epsb = __float_as_uint(rt.sign0 == 0 ? 0.f : eps);  // the clean pass of forward differences adds +-0
   Words zc[CT];  // regenerated signs: the Philox block of the column's current 128 k
   // eps z of column tile c of buffer b: 8 consecutive k from 8 kg
   auto probe_values = [&](const Buf& b, int c, float (&ez)[8]) {
     if constexpr (T::kZ) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) ez[e] = b.z[c][e >> 2][e & 3];
+      for (int e = 0; e < 8; ++e) ez[e] = NS == 1 && rt.sign0 == 0 ? 0.f : b.z[c][e >> 2][e & 3];
     } else if constexpr (T::kind == ZO_GAUSSIAN) {
       const bool second = b.g >= kt0;
       const uint64_t j = (second ? s1.zoff : s0.zoff) + (uint64_t)(row0 + rel[c]) * (uint64_t)(second ? s1.K : s0.K) +
@@ -360,7 +370,7 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
       gauss_block(key, probe, j >> 2, z);
       gauss_block(key, probe, (j >> 2) + 1, z + 4);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) ez[e] = fmul(eps, z[e]);
+      for (int e = 0; e < 8; ++e) ez[e] = fmul(__uint_as_float(epsb), z[e]);
     } else {
       // flag pair d of this lane's 8: bits 4 kg + d and 16 + 4 kg + d of the unshuffled word
       uint32_t word;
@@ -377,12 +387,11 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
         const uint32_t q = (uint32_t)(j >> 5) & 3u;
         word = sign_word_unshuffle(q == 0 ? zc[c].w[0] : q == 1 ? zc[c].w[1] : q == 2 ? zc[c].w[2] : zc[c].w[3]);
       }
-      const uint32_t u = ~(word >> (4 * kg));  // bit set: z = -1
-      const uint32_t e0 = __float_as_uint(eps);
+      const uint32_t u = word >> (4 * kg);  // bit set: z = +1
 #pragma unroll
       for (int d = 0; d < 4; ++d) {
-        ez[2 * d] = __uint_as_float(((u << (31 - d)) & 0x80000000u) | e0);
-        ez[2 * d + 1] = __uint_as_float(((u << (15 - d)) & 0x80000000u) | e0);
+        ez[2 * d] = __uint_as_float(sign_of(u << (31 - d), epsb));
+        ez[2 * d + 1] = __uint_as_float(sign_of(u << (15 - d), epsb));
       }
     }
   };
@@ -409,7 +418,6 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
         acc[h * RT + i][c] =
             __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i][PA[q]], B[PB[q]], acc[h * RT + i][c], 0, 0, 0);
   };
-  const float s0f = (float)rt.sign0;  // 0 for the clean pass of forward differences
   auto compute = [&](const Buf& b, const uint8_t* st, int ks) {
     auto load_a = [&](b8 (&A)[RT][3], int h) {
 #pragma unroll
@@ -420,13 +428,7 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
     };
     float ez[CT][8];
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
-      probe_values(b, c, ez[c]);
-      if constexpr (NS == 1) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) ez[c][e] = s0f == 0.f ? 0.f : ez[c][e];
-      }
-    }
+    for (int c = 0; c < CT; ++c) probe_values(b, c, ez[c]);
     auto weight = [&](int c, int h, float (&t)[8]) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -469,7 +471,12 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
         }
       }
     } else {
-      b8 B[CT][3];
+      b8 B[CT][3], A[2][RT][3];
+      if constexpr (RT <= 2) {  // (more row tiles: too many registers)
+        load_a(A[0], 0);
+        load_a(A[1], 1);
+        __builtin_amdgcn_sched_barrier(0x7);  // arithmetic may move across, LDS reads may not
+      }
 #pragma unroll
       for (int c = 0; c < CT; ++c) {
         float t[8];
@@ -478,10 +485,9 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
       }
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        b8 A[RT][3];
-        load_a(A, h);
+        if constexpr (RT > 2) load_a(A[h], h);
 #pragma unroll
-        for (int c = 0; c < CT; ++c) mma(A, B[c], h, c);
+        for (int c = 0; c < CT; ++c) mma(A[h], B[c], h, c);
       }
     }
   };
@@ -496,6 +502,7 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
 #pragma unroll
   for (int g = 0; g < PD; ++g) load_b(buf[g], g);
   asm volatile("" ::: "memory");
+  init();  // waits for loads older than these only
   wait_and_barrier<PD * T::LPT>();
   auto stage = [&](auto parity, int s) {
     constexpr int P = decltype(parity)::value;
@@ -517,8 +524,29 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
   wait_and_barrier<0>();  // the copies past the last stage have landed: the stages are free
 }
 
-__device__ __forceinline__ float sigmoidf_(float x) { return 1.0f / (1.0f + __expf(-x)); }
-__device__ __forceinline__ float tanhf_(float x) { return 1.0f - 2.0f / (__expf(2.0f * x) + 1.0f); }
+// 1 / d for d >= 1 (up to infinity) to within one rounding: the hardware's
+// reciprocal and one Newton step (IEEE division takes 10 instructions, and an
+// LSTM cell has five). d is held below 2^126 first, where the step's 1 - d r
+// would be 0 times infinity; minimum keeps a NaN.
+__device__ __forceinline__ float rcp_ge1(float d) {
+  d = __builtin_elementwise_minimum(d, 0x1p126f);
+  const float r = __builtin_amdgcn_rcpf(d);
+  return fmaf(fmaf(-d, r, 1.0f), r, r);
+}
+__device__ __forceinline__ float sigmoidf_(float x) { return rcp_ge1(1.0f + __expf(-x)); }
+__device__ __forceinline__ float tanhf_(float x) { return fmaf(-2.0f, rcp_ge1(__expf(2.0f * x) + 1.0f), 1.0f); }
+
+// acc = bias + s eps z of each column, for the rows of each sign.
+template <typename T>
+__device__ __forceinline__ void bias_init(f4 (&acc)[T::RTT][T::CT], const float (&bias)[T::CT], const float (&zb)[T::CT],
+                                          int sign0) {
+#pragma unroll
+  for (int ct = 0; ct < T::CT; ++ct) {
+    const float v0 = sign0 == 0 ? bias[ct] : bias[ct] + zb[ct], v1 = T::NS == 2 ? bias[ct] - zb[ct] : v0;
+#pragma unroll
+    for (int i = 0; i < T::RTT; ++i) acc[i][ct] = i < T::RT ? f4{v0, v0, v0, v0} : f4{v1, v1, v1, v1};
+  }
+}
 
 // 32 rows (row tiles 2 c, 2 c + 1) of the accumulators into ep[32][kEpRow],
 // column 16 CT wave + 16 ct + lane % 16.
@@ -581,23 +609,22 @@ __global__ __launch_bounds__(NT, 2) void gate_f32_kernel(GateArgs g) {
     for (int e = 0; e < UPT; ++e) cprev[c][e] = cp[e];
   }
   f4 acc[RTT][CT];
-  {
-    const float* bias = g.theta + gl.off_b + (int64_t)wave * H + u0 + (lane & 15);
-    const float* zb = gl.zb + ((int64_t)rt.probe * 4 + wave) * H + u0 + (lane & 15);
+  // the bias (with its probe term) of this lane's columns, into the
+  // accumulators once the main loop's first loads are on their way
+  float bias[CT], zb[CT];
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      const float b = bias[16 * ct], z = zb[16 * ct];
-      const float v0 = rt.sign0 == 0 ? b : b + z, v1 = T::NS == 2 ? b - z : v0;
-#pragma unroll
-      for (int i = 0; i < RTT; ++i) acc[i][ct] = i < RT ? f4{v0, v0, v0, v0} : f4{v1, v1, v1, v1};
-    }
+  for (int ct = 0; ct < CT; ++ct) {
+    const int64_t u = u0 + 16 * ct + (lane & 15);
+    bias[ct] = g.theta[gl.off_b + (int64_t)wave * H + u];
+    zb[ct] = gl.zb[((int64_t)rt.probe * 4 + wave) * H + u];
   }
+  auto init = [&]() { bias_init<T>(acc, bias, zb, rt.sign0); };
   const uint64_t zpos = (uint64_t)rt.probe * g.zc_stride;
   const Seg s0{gl.x, g.theta + gl.off_ih, gl.off_ih, gl.El, T::kZ ? gl.zc_ih + zpos : nullptr};
   const Seg s1{gl.hprev, g.theta + gl.off_hh, gl.off_hh, H, T::kZ ? gl.zc_hh + zpos : nullptr};
   mainloop<T, kSplit>(
       acc, s0, s1, 2, rt, __builtin_amdgcn_readfirstlane(wave * H + u0), [&](int ct) { return 16 * ct + (lane & 15); }, g.key,
-      g.i0 + (uint32_t)rt.probe, g.eps, T::kBits ? g.bits + (uint64_t)rt.probe * g.bits_stride : nullptr, st0, st1);
+      g.i0 + (uint32_t)rt.probe, g.eps, T::kBits ? g.bits + (uint64_t)rt.probe * g.bits_stride : nullptr, st0, st1, init);
 #pragma unroll
   for (int c = 0; c < RTT / 2; ++c) {
     float* ep = (float*)(c & 1 ? st1 : st0);
@@ -695,17 +722,17 @@ __global__ __launch_bounds__(NT, 2) void head_f32_kernel(HeadArgs g) {
   f4 acc[RTT][CT];
   const int row0 = __builtin_amdgcn_readfirstlane(min(v0 + 16 * CT * wave, V - 1));
   auto col = [&](int ct) { return min(16 * ct + (lane & 15), V - 1 - row0); };
+  float bias[CT], zb[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
-    const float b = g.theta[g.off_b + (uint64_t)(row0 + col(ct))], z = g.zbo[(int64_t)rt.probe * V + row0 + col(ct)];
-    const float v0f = rt.sign0 == 0 ? b : b + z, v1f = T::NS == 2 ? b - z : v0f;
-#pragma unroll
-    for (int i = 0; i < RTT; ++i) acc[i][ct] = i < RT ? f4{v0f, v0f, v0f, v0f} : f4{v1f, v1f, v1f, v1f};
+    bias[ct] = g.theta[g.off_b + (uint64_t)(row0 + col(ct))];
+    zb[ct] = g.zbo[(int64_t)rt.probe * V + row0 + col(ct)];
   }
+  auto init = [&]() { bias_init<T>(acc, bias, zb, rt.sign0); };
   const Seg s0{g.h, g.theta + g.off_w, g.off_w, g.H,
                T::kZ ? g.zc_out + (uint64_t)rt.probe * g.zc_stride : nullptr};
   mainloop<T, kSplit>(acc, s0, s0, 1, rt, row0, col, g.key, g.i0 + (uint32_t)rt.probe, g.eps,
-                      T::kBits ? g.bits + (uint64_t)rt.probe * g.bits_stride : nullptr, st0, st1);
+                      T::kBits ? g.bits + (uint64_t)rt.probe * g.bits_stride : nullptr, st0, st1, init);
 #pragma unroll
   for (int c = 0; c < RTT / 2; ++c) {
     float* ep = (float*)(c & 1 ? st1 : st0);

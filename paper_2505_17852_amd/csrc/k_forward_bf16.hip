@@ -17,13 +17,19 @@
 // theta +- eps z is never formed. For small eps the two-stream form
 // acc += A . W; acc += A . (s eps z) is used instead (kSplit).
 //
-// Tiles: a workgroup of 8 waves computes TM rows x TN columns, TM x TN =
-// 65536 (TN = kVocabTileWide, 256: 256 x 256); its waves split the
-// columns into TN / 64 wave columns and the rows into 8 / (TN / 64) wave
-// rows, each wave computing 128 rows x 64 columns (4 x 2 tiles of 32x32 MFMA
-// output). Two waves share each SIMD, so one wave's loads, probe expansion
-// and address work run under the other's matrix instructions. Lane l feeds
-// row/column l % 32 and k block l / 32.
+// Tiles: a workgroup computes TM rows x TN columns (256 x 256, 128 x 256 or 64
+// x 256 with 8 waves; the gate also 64 x 128 with 4); its waves split the
+// columns into TN / 64 wave columns and the rows into two wave rows, each wave
+// computing TM / 2 rows x 64 columns (TM / 64 x 2 tiles of 32x32 MFMA output).
+// Two waves share each SIMD, so one wave's loads, probe expansion and address
+// work run under the other's matrix instructions. Lane l feeds row/column l %
+// 32 and k block l / 32. The small tiles are for launches that 256-row tiles
+// would leave on a few CUs or fill with padding (pick_tiles): a 2-layer model
+// of 768 units with 4 probes and a batch of 48 (48 workgroups of 256 rows, a
+// third of them padding) takes 4.90 -> 1.86 ms per step, 512 units with one
+// probe 1.31 -> 0.55 ms, 1,024 units with 64 probes and a batch of 32 7.8 ->
+// 3.7 ms, the large model's forward differences (17 row blocks of 64 column
+// blocks: a quarter of a fifth round) 38.9 -> 37.6 ms per 4 positions.
 //
 // Operands. The activations (A) pass through LDS: each K tile of the TM rows
 // is copied from global memory straight into LDS (buffer loads with the LDS
@@ -48,6 +54,7 @@
 
 #include <type_traits>
 
+#include "zo_cell.hpp"
 #include "zo_kernels.hpp"
 #include "zo_pack.hpp"
 #include "zo_profile.hpp"
@@ -61,13 +68,18 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t Rsrc;
 
-constexpr int TM = 65536 / kVocabTileWide;  // rows per workgroup (kVocabTileWide columns)
-constexpr int NWAVES = 8;
-constexpr int NT = 64 * NWAVES;  // threads per workgroup
-
-// Per probe kind: K tile, LDS layout, copy roles, B-operand prefetch depth.
-template <int kind>
+// Per probe kind and workgroup tile (TM rows x TN columns): waves, K tile, LDS
+// layout, copy roles, B-operand prefetch depth.
+template <int kind, int TM_, int TN_>
 struct Tiles {
+  static constexpr int TM = TM_, TN = TN_;
+  static constexpr int WAVES_N = TN / 64;  // wave tiles are 64 columns wide
+  static constexpr int WAVES_M = 2;
+  static constexpr int NWAVES = WAVES_M * WAVES_N;
+  static constexpr int NT = 64 * NWAVES;  // threads per workgroup
+  static constexpr int WROWS = TM / WAVES_M;  // rows per wave tile
+  static constexpr int MT = WROWS / 32;
+  static constexpr int WCOLS = 64, NTW = 2;
   static constexpr bool kSigns = kind == ZO_RADEMACHER || kind == kSignsCached;
   static constexpr bool kBits = kind == kSignsCached;      // sign words read from the sign-probe cache
   static constexpr bool kZDirect = kind == kGaussCached;  // probe fragments loaded like the weights
@@ -77,11 +89,6 @@ struct Tiles {
   static constexpr int SW = TK / 32;                       // sign words per column and tile
   static constexpr int RowBytes = TK * 2;                  // one LDS row: TK fp16
   static constexpr int ABytes = TM * RowBytes;
-  static constexpr int TN = kVocabTileWide;
-  static constexpr int WAVES_N = TN / 64;  // wave tiles are 64 columns wide
-  static constexpr int WAVES_M = NWAVES / WAVES_N;
-  static constexpr int WROWS = TM / WAVES_M;  // rows per wave tile
-  static constexpr int MT = WROWS / 32;
   static constexpr int ZTileBytes = TN * RowBytes;
   static constexpr int StageBytes = ABytes + (kZTile ? ZTileBytes : 0);
   static constexpr int ACopies = ABytes / 1024 / NWAVES;  // activation copies per wave and tile
@@ -99,43 +106,40 @@ struct Tiles {
   static constexpr int ZROW_T = NT / TN;
   static constexpr int ZVALS = TK / ZROW_T;
   static constexpr int WPT = ZVALS / 32;  // sign words (or blocks of 32 normals) per thread and tile
-  static_assert(WAVES_M * WAVES_N == NWAVES && WROWS % 32 == 0, "wave grid");
+  static_assert(TN % 64 == 0 && WROWS % 32 == 0, "wave grid");
   static_assert(ACopies * NWAVES * 1024 == ABytes, "copy split");
   static_assert((2 * KSTEPS) % SLOTS == 0 && SLOTS <= 8, "the B slots repeat every two tiles");
   static_assert(ZVALS % 32 == 0 && ZROW_T * TN == NT, "probe roles: whole 32-k sign words per thread");
-  static_assert(kRowGranuleBF16 % WROWS == 0, "a wave tile lies inside one sign's rows");
   static_assert(RowBytes == 128, "swizzle of 128-byte rows (act_swizzle)");
 };
-static_assert(2 * kRowGranuleBF16 % TM == 0, "a probe's rows must be a whole number of row tiles");
-static_assert(TM % 128 == 0 && TM * kVocabTileWide == 65536, "workgroup tile");
 
 // LDS stages (static, so that every offset is a constant): activation tile
 // and probe tile (regenerated normal probes), or the activation tile alone
 // (sign probes, whose words have arrays of their own, and cached normal
-// probes).
-__shared__ __align__(16) uint8_t lds_s0[Tiles<ZO_GAUSSIAN>::StageBytes];
-__shared__ __align__(16) uint8_t lds_s1[Tiles<ZO_GAUSSIAN>::StageBytes];
-__shared__ __align__(16) uint8_t lds_c0[Tiles<kGaussCached>::StageBytes];
-__shared__ __align__(16) uint8_t lds_c1[Tiles<kGaussCached>::StageBytes];
-static_assert(Tiles<ZO_RADEMACHER>::StageBytes == Tiles<kGaussCached>::StageBytes, "activation-only stages");
-static_assert(Tiles<kSignsCached>::StageBytes == Tiles<kGaussCached>::StageBytes, "activation-only stages");
-static_assert(2 * sizeof(lds_s0) <= 160 * 1024, "LDS");
+// probes); sized per tile shape, so that small workgroups share a CU.
+template <typename T>
+__shared__ __align__(16) uint8_t lds_stage0[T::StageBytes];
+template <typename T>
+__shared__ __align__(16) uint8_t lds_stage1[T::StageBytes];
 // Sign words of a K tile (two per workgroup column, unshuffled), per stage,
 // in arrays of their own: the compiler orders an LDS store after every copy
 // in flight into the same array.
-constexpr int kWordBytes = kVocabTileWide * 2 * 4;
-__shared__ __align__(16) uint8_t lds_words0[kWordBytes];
-__shared__ __align__(16) uint8_t lds_words1[kWordBytes];
+template <typename T>
+__shared__ __align__(16) uint8_t lds_words0[T::TN * 2 * 4];
+template <typename T>
+__shared__ __align__(16) uint8_t lds_words1[T::TN * 2 * 4];
 // Cached sign words: a ring of four tiles' words (tile t in buffer t % 4).
-__shared__ __align__(16) uint8_t lds_wring[4 * kWordBytes];
+template <typename T>
+__shared__ __align__(16) uint8_t lds_wring[4 * T::TN * 2 * 4];
 
 // The gate's cell states c of its tile (TM rows x the TN / 4 hidden units of
 // its columns, row-major), fetched before the main loop so that the cell
 // update reads them from LDS; kinds whose stages leave room for it (not the
 // regenerated normal probes' activation + probe stages).
-constexpr int kCellCols = kVocabTileWide / 4;
-__shared__ __align__(16) float lds_gc[TM * kCellCols];
-static_assert(2 * sizeof(lds_c0) + 2 * kWordBytes + sizeof(lds_gc) <= 160 * 1024, "LDS");
+template <typename T>
+__shared__ __align__(16) float lds_gc[T::TM * T::TN / 4];
+static_assert(2 * Tiles<kSignsCached, 256, 256>::StageBytes + 4 * 256 * 8 + 256 * 64 * 4 <= 160 * 1024, "LDS");
+static_assert(2 * Tiles<ZO_GAUSSIAN, 256, 256>::StageBytes <= 160 * 1024, "LDS");
 
 // The head's bias values of its vocabulary tile, fetched before the main
 // loop so that the epilogue finds them in LDS: 256 words of theta from the
@@ -146,30 +150,19 @@ __shared__ __align__(16) float lds_hzbo[kVocabTileWide];
 // bias + s eps z of each column for the rows of each sign (-inf past V)
 __shared__ __align__(16) float lds_hadd[2][kVocabTileWide];
 // the target token of each row of the head's tile (-1 for padding rows)
-__shared__ __align__(16) int lds_htgt[TM];
+template <typename T>
+__shared__ __align__(16) int lds_htgt[T::TM];
 
-template <int kind, int S>
+template <typename T, int S>
 __device__ __forceinline__ uint8_t* stage() {
   static_assert(S == 0 || S == 1, "stage index");
-  if constexpr (!Tiles<kind>::kZTile)
-    return S == 0 ? lds_c0 : lds_c1;
-  else
-    return S == 0 ? lds_s0 : lds_s1;
+  return S == 0 ? lds_stage0<T> : lds_stage1<T>;
 }
-template <int S>
+template <typename T, int S>
 __device__ __forceinline__ uint8_t* words4() {
   static_assert(S == 0 || S == 1, "stage index");
-  return S == 0 ? lds_words0 : lds_words1;
+  return S == 0 ? lds_words0<T> : lds_words1<T>;
 }
-
-// The workgroup geometry of the loop, as the gate and head epilogues use it:
-// 8 waves, 2 row halves x 4 column quarters, wave tiles of 128 rows x 64
-// columns (4 x 2 tiles of 32x32).
-struct Geo {
-  static constexpr int WAVES_M = Tiles<ZO_GAUSSIAN>::WAVES_M, WAVES_N = Tiles<ZO_GAUSSIAN>::WAVES_N;
-  static constexpr int WROWS = Tiles<ZO_GAUSSIAN>::WROWS, WCOLS = 64;
-  static constexpr int MT = Tiles<ZO_GAUSSIAN>::MT, NTW = 2;
-};
 
 __device__ __forceinline__ h8 as_h8(u4 v) { return __builtin_bit_cast(h8, v); }
 
@@ -277,11 +270,11 @@ struct BitsB {
 // instead of acc += A.fp16(W + s eps z): a weight fragment rounded with the
 // probe added loses up to half an fp16 ulp of w per element, which is a
 // large share of eps z once eps is small against |w|.
-template <int kind, bool kTrans = false, bool kSplit = false, typename ColMap>
-__device__ __forceinline__ void mainloop_bf16(f16v (&acc)[Tiles<kind>::MT][2], const SegB s0, const SegB s1,
+template <int kind, typename T, bool kTrans = false, bool kSplit = false, typename ColMap>
+__device__ __forceinline__ void mainloop_bf16(f16v (&acc)[T::MT][2], const SegB s0, const SegB s1,
                                               int nseg, int64_t cb0, ColMap colmap, Key key, uint32_t probe,
                                               int sgn, float eps, uint16_t eps_b, const BitsB bits) {
-  using T = Tiles<kind>;
+  constexpr int TM = T::TM, NWAVES = T::NWAVES, kWordBytes = T::TN * 2 * 4;
   static_assert(!(kSplit && T::kPerturbed), "the perturbed-weight cache holds the fused form only");
   constexpr int MT = T::MT;
   constexpr int TK = T::TK;
@@ -397,13 +390,13 @@ __device__ __forceinline__ void mainloop_bf16(f16v (&acc)[Tiles<kind>::MT][2], c
     const uint64_t j0 = sg.zoff + (uint64_t)zn * (uint64_t)sg.ldw + kt;
     return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rbits, sign_word_offset(j0), 0, 0));
   };
-  auto put_words = [&](int ti, uint2 w) { *(uint2*)(lds_wring + (ti & 3) * kWordBytes + zr * 8) = w; };
+  auto put_words = [&](int ti, uint2 w) { *(uint2*)(lds_wring<T> + (ti & 3) * kWordBytes + zr * 8) = w; };
 
   // The next K tile's activation copies into stage S (the last loads of a
   // tile before its B loads: the count wait_and_barrier leaves in flight).
   auto issue_copies = [&](auto stage_tag) {
     constexpr int S = decltype(stage_tag)::value;
-    uint8_t* base = stage<kind, S>();
+    uint8_t* base = stage<T, S>();
     const bool second = seg != 0;
     const uint32_t lda2 = second ? lda2_1 : lda2_0;
 #pragma unroll
@@ -435,10 +428,10 @@ __device__ __forceinline__ void mainloop_bf16(f16v (&acc)[Tiles<kind>::MT][2], c
           word = rademacher_word(key, probe, j >> 5);
         }
         // the word of column zr's 32 k at 32 (WPT zpart + i), unshuffled
-        *(uint32_t*)(words4<S>() + zr * 8 + (T::WPT * zpart + i) * 4) = sign_word_unshuffle(word);
+        *(uint32_t*)(words4<T, S>() + zr * 8 + (T::WPT * zpart + i) * 4) = sign_word_unshuffle(word);
       }
     } else if constexpr (T::kZTile) {
-      uint8_t* zrow = stage<kind, S>() + T::ABytes + zr * T::RowBytes;
+      uint8_t* zrow = stage<T, S>() + T::ABytes + zr * T::RowBytes;
 #pragma unroll 2
       for (int c = 0; c < 4 * T::WPT; ++c) {
         float za[4], zb[4];
@@ -480,7 +473,7 @@ __device__ __forceinline__ void mainloop_bf16(f16v (&acc)[Tiles<kind>::MT][2], c
   auto compute = [&](auto stage_tag, int it) {
     constexpr int S = decltype(stage_tag)::value;
     constexpr std::integral_constant<int, 1 - S> next{};
-    const uint8_t* base = stage<kind, S>();
+    const uint8_t* base = stage<T, S>();
     const uint8_t* pa = base + a_lane;
     const uint8_t* pz = base + T::ABytes + z_lane;
     // the B tiles this tile's steps load from: it + kQ0 .. it + kQ1
@@ -493,9 +486,9 @@ __device__ __forceinline__ void mainloop_bf16(f16v (&acc)[Tiles<kind>::MT][2], c
       for (int nt = 0; nt < 2; ++nt) {
         const uint8_t* wsrc;
         if constexpr (T::kBits)
-          wsrc = lds_wring + (it & 3) * kWordBytes;
+          wsrc = lds_wring<T> + (it & 3) * kWordBytes;
         else
-          wsrc = words4<S>();
+          wsrc = words4<T, S>();
         const uint2 wd = *(const uint2*)(wsrc + w_lane + 32 * 8 * nt);
         us[nt][0] = (wd.x ^ flip) >> lshift;
         us[nt][1] = (wd.y ^ flip) >> lshift;
@@ -649,13 +642,11 @@ __device__ __forceinline__ void tile_of(int L, int nm, int nn, int& m, int& n) {
   m = x * per + g * R + (rem - n * R);
 }
 
-__device__ __forceinline__ float sigm(float x) { return 1.0f / (1.0f + __expf(-x)); }
-__device__ __forceinline__ float tanh_(float x) { return 1.0f - 2.0f / (__expf(2.0f * x) + 1.0f); }
-
 // Row (within the workgroup's TM) of accumulator element v of row tile mt
 // for this lane: 32x32 MFMA output layout.
+template <typename T>
 __device__ __forceinline__ int acc_row(int wm, int mt, int lg, int v) {
-  return Geo::WROWS * wm + 32 * mt + 8 * (v >> 2) + 4 * lg + (v & 3);
+  return T::WROWS * wm + 32 * mt + 8 * (v >> 2) + 4 * lg + (v & 3);
 }
 
 template <int MT, int NTW>
@@ -681,7 +672,8 @@ struct GateArgsB {
   float eps;
   uint16_t eps_b;
   RowMap rm;
-  int n_row_blocks;  // M / TM
+  int row0;          // first row of the launch (a multiple of its tile's rows)
+  int n_row_blocks;  // row blocks of the launch
   const uint16_t* zc_ih;  // probe cache: W_ih's and W_hh's values of probe 0; probe n at + n * zc_stride
   const uint16_t* zc_hh;
   uint64_t zc_stride;
@@ -697,17 +689,17 @@ struct GateArgsB {
 // units, so lane lr holds gates i, g (lr < 16) or f, o (lr >= 16) of unit
 // lr % 16 in the pair, and one exchange with lane lr ^ 16 brings all four
 // gates of a (row, unit) together.
-template <int kind, bool kFD, bool kSplit>
-__global__ __launch_bounds__(NT, 1) void gate_bf16_kernel(GateArgsB g) {
-  using G = Geo;
-  constexpr int TN = kVocabTileWide;
+template <int kind, typename T, bool kSplit>
+__global__ __launch_bounds__(T::NT, T::NT == 256 ? 3 : 1) void gate_bf16_kernel(GateArgsB g) {
+  using G = T;
+  constexpr int TM = T::TM, TN = T::TN, kCellCols = TN / 4;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave % G::WAVES_M, wn = wave / G::WAVES_M;
   const int lr = lane & 31, lg = lane >> 5;
   int mb, nb;
   tile_of(blockIdx.x, g.n_row_blocks, (4 * g.H + TN - 1) / TN, mb, nb);
   const int u0 = nb * (TN / 4);
-  const int64_t m0 = (int64_t)mb * TM;
+  const int64_t m0 = g.row0 + (int64_t)mb * TM;
   const int pair = pass_of(g.rm, m0).probe;
   const int sgn = pass_of(g.rm, m0 + G::WROWS * wm).sign;  // a wave tile lies inside one pass
   const int H = g.H;
@@ -731,21 +723,21 @@ __global__ __launch_bounds__(NT, 1) void gate_bf16_kernel(GateArgsB g) {
                 H, H, kind == kGaussCached ? g.zc_hh + zpos : nullptr};
   const BitsB bits{kind == kSignsCached ? g.bits + (uint64_t)pair * g.bits_stride : nullptr,
                    (uint32_t)(g.bits_stride * 4)};
-  constexpr bool kCellLds = !Tiles<kind>::kZTile;
+  constexpr bool kCellLds = !T::kZTile;
   if constexpr (kCellLds) {
-    // the tile's cell states into LDS: 1 KB copies of 4 rows (16 lanes of 16
-    // bytes per row), copy j of wave w is copy 8 j + w of the 64; issued
-    // before the loop's first loads, so its first barrier waits for them
-    static_assert(TM * kCellCols * 4 == 64 * 1024 && kCellCols == 64, "cell tile copies");
+    // the tile's cell states into LDS: 1 KB copies of whole rows, copy j of
+    // wave w is copy NWAVES j + w; issued before the loop's first loads, so
+    // its first barrier waits for them
+    static_assert(TM * kCellCols * 4 % (1024 * T::NWAVES) == 0, "cell tile copies");
     const Rsrc rc = make_rsrc(g.cst + m0 * H, (uint32_t)TM * (uint32_t)H * 4u);
     const int w = __builtin_amdgcn_readfirstlane(wave);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int cp = 8 * j + w;
-      copy_to_lds(rc, cell_copy_offset(cp, lane, H, u0), 0u, (uint8_t*)lds_gc + 1024 * cp);
+    for (int j = 0; j < TM * kCellCols * 4 / 1024 / T::NWAVES; ++j) {
+      const int cp = T::NWAVES * j + w;
+      copy_to_lds(rc, cell_copy_offset(cp, lane, H, u0, kCellCols), 0u, (uint8_t*)lds_gc<T> + 1024 * cp);
     }
   }
-  mainloop_bf16<kind, false, kSplit>(acc, s0, s1, 2, (TN / kPackBlockCols) * (int64_t)nb, colmap, g.key,
+  mainloop_bf16<kind, T, false, kSplit>(acc, s0, s1, 2, (TN / kPackBlockCols) * (int64_t)nb, colmap, g.key,
                                      g.i0 + (uint32_t)pair, sgn, g.eps, g.eps_b, bits);
 
   constexpr int NP = G::NTW / 2;  // unit groups per wave
@@ -782,12 +774,12 @@ __global__ __launch_bounds__(NT, 1) void gate_bf16_kernel(GateArgsB g) {
         }
         const float ip = hi ? got[0] : mine[0], fp = hi ? mine[0] : got[0];
         const float gp = hi ? got[1] : mine[1], op = hi ? mine[1] : got[1];
-        const int lrow = acc_row(wm, mt, lg, v + hi);
+        const int lrow = acc_row<T>(wm, mt, lg, v + hi);
         const int64_t o = (m0 + lrow) * H + u[p];
-        const float cprev = kCellLds ? lds_gc[lrow * kCellCols + (u[p] - u0)] : g.cst[o];
-        const float c = sigm(fp) * cprev + sigm(ip) * tanh_(gp);
+        float c = kCellLds ? lds_gc<T>[lrow * kCellCols + (u[p] - u0)] : g.cst[o];
+        const float h = lstm_cell(ip, fp, gp, op, c);
         g.cst[o] = c;
-        g.hout[o] = f16_bits(sigm(op) * tanh_(c));
+        g.hout[o] = f16_bits(h);
       }
     }
   }
@@ -819,10 +811,11 @@ struct HeadArgsB {
   uint64_t bits_stride;
 };
 
-template <int kind, bool kFD, bool kSplit>
-__global__ __launch_bounds__(NT, 1) void head_bf16_kernel(HeadArgsB g) {
-  using G = Geo;
-  constexpr int TN = kVocabTileWide;
+template <int kind, typename T, bool kSplit>
+__global__ __launch_bounds__(T::NT, 1) void head_bf16_kernel(HeadArgsB g) {
+  using G = T;
+  constexpr int TM = T::TM, TN = T::TN, NT = T::NT;
+  static_assert(TN == kVocabTileWide, "vocabulary tile");
   constexpr int NTW = G::NTW;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave % G::WAVES_M, wn = wave / G::WAVES_M;
@@ -882,7 +875,7 @@ __global__ __launch_bounds__(NT, 1) void head_bf16_kernel(HeadArgsB g) {
     const int b = pass_of(g.rm, r0 + t).b;
     if (b < g.B) tgt_tok = g.tokens[(int64_t)b * (g.C + 1) + g.t0 + tt + 1];
   }
-  mainloop_bf16<kind, true, kSplit>(acc, s0, s0, 1, (TN / kPackBlockCols) * (int64_t)vt, colmap, g.key,
+  mainloop_bf16<kind, T, true, kSplit>(acc, s0, s0, 1, (TN / kPackBlockCols) * (int64_t)vt, colmap, g.key,
                                     g.i0 + (uint32_t)pair, sgn, g.eps, g.eps_b, bits);
 
   // transposed tiles: acc[mt][nt][v] is the logit of activation row
@@ -898,7 +891,7 @@ __global__ __launch_bounds__(NT, 1) void head_bf16_kernel(HeadArgsB g) {
     const int sg = pass_of(g.rm, r0 + G::WROWS * half).sign;
     const float b = bf16_to_f32(*(const uint16_t*)(lds_hbias + bias_lead + 2 * c));
     lds_hadd[half][c] = v0 + c < V ? b + (float)sg * lds_hzbo[c] : -INFINITY;
-    if (t < TM) lds_htgt[t] = tgt_tok;
+    if (t < TM) lds_htgt<T>[t] = tgt_tok;
   }
   __syncthreads();
   float add[NTW][16];
@@ -914,12 +907,12 @@ __global__ __launch_bounds__(NT, 1) void head_bf16_kernel(HeadArgsB g) {
     }
   }
   // cross-wave reduction in the first stage buffer (free after the loop)
-  float* red_m = (float*)stage<kind, 0>();  // [WAVES_N][TM]
+  float* red_m = (float*)stage<T, 0>();  // [WAVES_N][TM]
   float* red_s = red_m + G::WAVES_N * TM;   // [WAVES_N][TM]
 #pragma unroll
   for (int mt = 0; mt < G::MT; ++mt) {
     const int lrow = G::WROWS * wm + 32 * mt + lr;
-    const int tgt = lds_htgt[lrow] - cbase;  // negative (never a held column) for padding rows
+    const int tgt = lds_htgt<T>[lrow] - cbase;  // negative (never a held column) for padding rows
     float mx = -INFINITY;
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt) {
@@ -970,7 +963,7 @@ __global__ __launch_bounds__(NT, 1) void head_bf16_kernel(HeadArgsB g) {
 #pragma unroll
     for (int w = 0; w < G::WAVES_N; ++w) {
       const float m = red_m[w * TM + t];
-      sum += m == -INFINITY ? 0.f : red_s[w * TM + t] * __expf(m - mx);
+      sum = m == -INFINITY ? sum : fmaf(red_s[w * TM + t], __expf(m - mx), sum);
     }
     g.pmax[(int64_t)vt * g.rows + rr0 + t] = mx;
     g.psum[(int64_t)vt * g.rows + rr0 + t] = sum;
@@ -1057,29 +1050,34 @@ __global__ __launch_bounds__(256) void embed_bf16_rad_kernel(const uint16_t* the
   for (int q = 0; q < 4; ++q) dst[q] = out[q];
 }
 
-// Calls go(kind, fd, split) with the compile-time variant of this call: the
+// The tiles of a launch of this call (cols columns): a tile lies inside one
+// probe's rows, a wave row inside one sign's.
+TilePlan plan_tiles(const ForwardArgs& a, int64_t rows, int64_t cols, bool gate) {
+  const int64_t fit = a.rows.fd ? a.rows.Bp : 2 * (int64_t)a.rows.Bp;
+  return pick_tiles(rows, cols, gate, fit % 256 == 0 ? 256 : fit % 128 == 0 ? 128 : 64);
+}
+
+// Calls go(kind, tm, split) with the compile-time variant of this call: the
 // probe kind (sign probes; normal probes read from the probe cache or
-// regenerated), central or forward differences, fused or two-stream products.
+// regenerated), the tile's rows, fused or two-stream products.
 template <typename Go>
-void dispatch_bf16(const ForwardArgs& a, Go&& go) {
+void dispatch_bf16(const ForwardArgs& a, int tm, Go&& go) {
   using std::integral_constant;
-  auto by_split = [&](auto kind_tag, auto fd_tag) {
-    if (a.split) go(kind_tag, fd_tag, integral_constant<bool, true>{});
-    else go(kind_tag, fd_tag, integral_constant<bool, false>{});
+  auto by_tm = [&](auto kind_tag, auto split_tag) {
+    if (tm == 256) go(kind_tag, integral_constant<int, 256>{}, split_tag);
+    else if (tm == 128) go(kind_tag, integral_constant<int, 128>{}, split_tag);
+    else go(kind_tag, integral_constant<int, 64>{}, split_tag);
   };
-  auto by_fd = [&](auto kind_tag) {
-    if (a.rows.fd) by_split(kind_tag, integral_constant<bool, true>{});
-    else by_split(kind_tag, integral_constant<bool, false>{});
+  auto by_split = [&](auto kind_tag) {
+    if (a.split) by_tm(kind_tag, integral_constant<bool, true>{});
+    else by_tm(kind_tag, integral_constant<bool, false>{});
   };
-  if (a.cfg.probe == ZO_RADEMACHER && a.bits) by_fd(integral_constant<int, kSignsCached>{});
-  else if (a.cfg.probe == ZO_RADEMACHER) by_fd(integral_constant<int, ZO_RADEMACHER>{});
-  else if (a.zc && !a.split) {
-    // perturbed weights hold the fused form only
-    if (a.rows.fd) go(integral_constant<int, kGaussPerturbed>{}, integral_constant<bool, true>{}, integral_constant<bool, false>{});
-    else go(integral_constant<int, kGaussPerturbed>{}, integral_constant<bool, false>{}, integral_constant<bool, false>{});
-  }
-  else if (a.zc) by_fd(integral_constant<int, kGaussCached>{});
-  else by_fd(integral_constant<int, ZO_GAUSSIAN>{});
+  if (a.cfg.probe == ZO_RADEMACHER && a.bits) by_split(integral_constant<int, kSignsCached>{});
+  else if (a.cfg.probe == ZO_RADEMACHER) by_split(integral_constant<int, ZO_RADEMACHER>{});
+  else if (a.zc && !a.split)  // perturbed weights hold the fused form only
+    by_tm(integral_constant<int, kGaussPerturbed>{}, integral_constant<bool, false>{});
+  else if (a.zc) by_split(integral_constant<int, kGaussCached>{});
+  else by_split(integral_constant<int, ZO_GAUSSIAN>{});
 }
 
 }  // namespace
@@ -1125,7 +1123,6 @@ hipError_t launch_gate_bf16(const ForwardArgs& a, int l, const void* x, const vo
   g.eps = a.eps;
   g.eps_b = f16_rne(a.eps);
   g.rm = row_map(R);
-  g.n_row_blocks = (int)(R.M / TM);
   g.w_ih16 = (const uint16_t*)a.w16 + a.zmap.ih[l];
   g.w_hh16 = (const uint16_t*)a.w16 + a.zmap.hh[l];
   g.zc_ih = a.zc ? (const uint16_t*)a.zc + a.zmap.ih[l] : nullptr;
@@ -1133,15 +1130,26 @@ hipError_t launch_gate_bf16(const ForwardArgs& a, int l, const void* x, const vo
   g.zc_stride = a.zmap.pg;
   g.bits = a.bits;
   g.bits_stride = bit_words(a.lay.total);
-  auto go = [&](auto kind_tag, auto fd_tag, auto split_tag) {
-    constexpr int kind = decltype(kind_tag)::value;
-    constexpr bool fd = decltype(fd_tag)::value;
-    constexpr bool split = decltype(split_tag)::value;
-    const dim3 grid((unsigned)(g.n_row_blocks * ((4 * g.H + kVocabTileWide - 1) / kVocabTileWide)));
-    ProfScope ps(kKGate, st);
-    gate_bf16_kernel<kind, fd, split><<<grid, NT, 0, st>>>(g);
+  const TilePlan plan = plan_tiles(a, R.M, 4 * (int64_t)g.H, true);
+  int64_t rows = 0;  // rows of the launch
+  auto go = [&](auto kind_tag, auto tm_tag, auto split_tag) {
+    constexpr int kind = decltype(kind_tag)::value, tm = decltype(tm_tag)::value;
+    using T = Tiles<kind, tm, tm == 64 ? 128 : 256>;
+    g.n_row_blocks = (int)(rows / tm);
+    const dim3 grid((unsigned)(g.n_row_blocks * ((4 * g.H + T::TN - 1) / T::TN)));
+    gate_bf16_kernel<kind, T, decltype(split_tag)::value><<<grid, T::NT, 0, st>>>(g);
   };
-  dispatch_bf16(a, go);
+  ProfScope ps(kKGate, st);
+  if (plan.rows > 0) {
+    g.row0 = 0;
+    rows = plan.rows;
+    dispatch_bf16(a, plan.tm, go);
+  }
+  if (plan.rows < R.M) {
+    g.row0 = (int)plan.rows;
+    rows = R.M - plan.rows;
+    dispatch_bf16(a, 64, go);
+  }
   return hipGetLastError();
 }
 
@@ -1176,15 +1184,14 @@ hipError_t launch_head_bf16(const ForwardArgs& a, const void* hist, int t0, int 
   h.zc_stride = a.zmap.pg;
   h.bits = a.bits;
   h.bits_stride = bit_words(a.lay.total);
-  const dim3 grid((unsigned)((int64_t)a.ws.nvt * (h.rows / TM)));
-  auto go = [&](auto kind_tag, auto fd_tag, auto split_tag) {
-    constexpr int kind = decltype(kind_tag)::value;
-    constexpr bool fd = decltype(fd_tag)::value;
-    constexpr bool split = decltype(split_tag)::value;
+  auto go = [&](auto kind_tag, auto tm_tag, auto split_tag) {
+    constexpr int kind = decltype(kind_tag)::value, tm = decltype(tm_tag)::value;
+    using T = Tiles<kind, tm, kVocabTileWide>;
+    const dim3 grid((unsigned)((int64_t)a.ws.nvt * (h.rows / tm)));
     ProfScope ps(kKHead, st);
-    head_bf16_kernel<kind, fd, split><<<grid, NT, 0, st>>>(h);
+    head_bf16_kernel<kind, T, decltype(split_tag)::value><<<grid, T::NT, 0, st>>>(h);
   };
-  dispatch_bf16(a, go);
+  dispatch_bf16(a, plan_tiles(a, h.rows, h.V, false).tm, go);
   return hipGetLastError();
 }
 

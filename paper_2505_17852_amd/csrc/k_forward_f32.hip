@@ -44,6 +44,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "zo_cell.hpp"
 #include "zo_kernels.hpp"
 #include "zo_pack.hpp"
 #include "zo_profile.hpp"
@@ -524,18 +525,6 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
   wait_and_barrier<0>();  // the copies past the last stage have landed: the stages are free
 }
 
-// 1 / d for d >= 1 (up to infinity) to within one rounding: the hardware's
-// reciprocal and one Newton step (IEEE division takes 10 instructions, and an
-// LSTM cell has five). d is held below 2^126 first, where the step's 1 - d r
-// would be 0 times infinity; minimum keeps a NaN.
-__device__ __forceinline__ float rcp_ge1(float d) {
-  d = __builtin_elementwise_minimum(d, 0x1p126f);
-  const float r = __builtin_amdgcn_rcpf(d);
-  return fmaf(fmaf(-d, r, 1.0f), r, r);
-}
-__device__ __forceinline__ float sigmoidf_(float x) { return rcp_ge1(1.0f + __expf(-x)); }
-__device__ __forceinline__ float tanhf_(float x) { return fmaf(-2.0f, rcp_ge1(__expf(2.0f * x) + 1.0f), 1.0f); }
-
 // acc = bias + s eps z of each column, for the rows of each sign.
 template <typename T>
 __device__ __forceinline__ void bias_init(f4 (&acc)[T::RTT][T::CT], const float (&bias)[T::CT], const float (&zb)[T::CT],
@@ -637,8 +626,8 @@ __global__ __launch_bounds__(NT, 2) void gate_f32_kernel(GateArgs g) {
       for (int e = 0; e < UPT; ++e) a[q][e] = ep[er * kEpRow + q * U + eu + e];
 #pragma unroll
     for (int e = 0; e < UPT; ++e) {
-      cn[e] = sigmoidf_(a[1][e]) * cprev[c][e] + sigmoidf_(a[0][e]) * tanhf_(a[2][e]);
-      h[e] = sigmoidf_(a[3][e]) * tanhf_(cn[e]);
+      cn[e] = cprev[c][e];
+      h[e] = lstm_cell(a[0][e], a[1][e], a[2][e], a[3][e], cn[e]);
     }
     if (cown[c]) {
       float* cp = gl.cst + crow[c] * H + u0 + eu;

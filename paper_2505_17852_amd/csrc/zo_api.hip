@@ -91,7 +91,7 @@ size_t zo_param_count(const zo_config* cfg) {
 
 // Both estimators' passes fit: central (2N passes) and forward (N + 1) differences.
 static zo::WsPlan plan_for(const zo_config* cfg, int32_t N, int32_t B, int32_t C, bool fd) {
-  return zo::plan_workspace(*cfg, zo::make_rows(N, B, zo::row_granule(*cfg, fd), fd), C);
+  return zo::plan_workspace(*cfg, zo::make_rows(N, B, zo::row_granule(*cfg, N, B, fd), fd), C);
 }
 
 size_t zo_workspace_bytes(const zo_config* cfg, int32_t N, int32_t B, int32_t C) {
@@ -141,7 +141,7 @@ static int forward_call(const zo_config* cfg, const void* theta, uint64_t seed, 
   if (N < 1 || B < 1 || C < 1) return fail(ZO_EINVAL, "N, B and C must be >= 1");
   if ((uint64_t)i0 + (uint64_t)N > 0x100000000ull)
     return fail(ZO_EINVAL, "probe indices i0 .. i0+N-1 must fit in 32 bits");
-  const zo::Rows rows = zo::make_rows(N, B, zo::row_granule(*cfg, fd), fd);
+  const zo::Rows rows = zo::make_rows(N, B, zo::row_granule(*cfg, N, B, fd), fd);
   if (rows.M > (int64_t)1 << 30) return fail(ZO_ESHAPE, "rows of all passes too many");
   const zo::WsPlan plan = zo::plan_workspace(*cfg, rows, C);
   // regen: the fixed scratch may lack room for the fp32 path's sign words

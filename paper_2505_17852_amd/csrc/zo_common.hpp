@@ -66,12 +66,87 @@ inline Layout make_layout(const zo_config& c) {
 //   forward differences (N + 1 passes): row r = p Bp + b, pass p < N at
 //     theta + eps z_p, pass N at theta itself (the clean pass).
 constexpr int kRowGranuleF32 = 16;   // fp32 path: the row tile of its MFMAs and of the packed states
-constexpr int kRowGranuleBF16 = 128; // bf16 path: 256-row tiles
 
-inline int row_granule(const zo_config& c, bool fd = false) {
+// Workgroup tiles of the bf16 path: 256, 128 or 64 rows (two wave rows of half
+// as many), 256 columns; the gate's 64-row tile has 128 columns. Every wave
+// row lies inside one sign's rows and every tile inside one probe's, so the
+// batch is padded to half the tile's rows (central differences) or to all of
+// them (forward differences).
+constexpr int kTileRows[3] = {256, 128, 64};
+
+// Cost of wgs workgroups of a tile, in units of one round of 256-row tiles (a
+// workgroup per CU). Measured with one shape forced at a time over models of
+// 512 to 4,096 units and 256 to 16,384 rows: a round of 128-row tiles takes
+// 0.62 of one of 256-row tiles, the gate's 64 x 128 tiles 0.32 for the first
+// 256 and 0.25 per 256 when three share a CU, the head's 64 x 256 ones 0.45.
+// (Every tile reads the same weight fragments per column, so smaller tiles
+// cost more per row; they win where 256-row tiles would leave CUs idle or
+// compute padding.)
+inline double tile_cost(int64_t wgs, int tm, bool gate) {
+  const double rounds = (double)((wgs + 255) / 256);
+  if (tm == 256) return rounds;
+  if (tm == 128) return 0.62 * rounds;
+  if (!gate) return 0.45 * rounds;
+  return wgs == 0 ? 0 : 0.25 * rounds > 0.32 ? 0.25 * rounds : 0.32;
+}
+inline int64_t tile_cols(int tm, bool gate) { return gate && tm == 64 ? 128 : 256; }
+
+// The tiles of a launch over `rows` rows and `cols` columns, at most max_tm
+// rows each: the first `rows` of the plan in tiles of tm rows and (gate) the
+// rest in 64-row tiles, where that fills a last round that tiles of tm rows
+// would leave nearly empty. Every tile shape gives the same bits.
+struct TilePlan {
+  int tm;
+  int64_t rows;
+};
+inline TilePlan pick_tiles(int64_t rows, int64_t cols, bool gate, int max_tm, double* cost = nullptr) {
+  TilePlan best{64, rows};
+  double least = 0;
+  for (int tm : kTileRows) {
+    if (tm > max_tm) continue;
+    const int64_t tn = tile_cols(tm, gate), nn = (cols + tn - 1) / tn, nm = rows / tm;
+    double c = tile_cost(nm * nn, tm, gate);
+    int64_t whole = nm;
+    if (gate && tm > 64) {
+      // whole rounds of tm-row tiles, the rest (64-row tiles) after them
+      const int64_t n1 = nm * nn / 256 * 256 / nn;
+      const int64_t rest = (rows - n1 * tm) / 64 * ((cols + 127) / 128);
+      const double split = tile_cost(n1 * nn, tm, true) + tile_cost(rest, 64, true) + 0.05;
+      if (n1 > 0 && n1 < nm && split < 0.97 * c) {
+        c = split;
+        whole = n1;
+      }
+    }
+    if (least == 0 || c < 0.97 * least) {
+      least = c;
+      best = TilePlan{tm, whole * tm};
+    }
+  }
+  if (cost) *cost = least;
+  return best;
+}
+
+// The multiple that batches are padded to. bf16 path: the one whose launches
+// cost least (per timestep: L gate launches of K = 2 H and a share of the
+// head's, K = H), the largest of equals.
+inline int row_granule(const zo_config& c, int32_t N, int32_t B, bool fd = false) {
   if (c.wdtype != ZO_WBF16) return kRowGranuleF32;
-  // forward differences: a whole 256-row tile inside one pass
-  return fd ? 2 * kRowGranuleBF16 : kRowGranuleBF16;
+  int best = 0;
+  double least = 0;
+  for (int tm : kTileRows) {
+    const int g = fd ? tm : tm / 2;
+    const int64_t Bp = ((int64_t)B + g - 1) / g * g;
+    const int64_t M = (fd ? (int64_t)N + 1 : 2 * (int64_t)N) * Bp;
+    double gate, head;
+    pick_tiles(M, 4 * (int64_t)c.hidden, true, tm, &gate);
+    pick_tiles(16 * M, c.vocab, false, tm, &head);
+    const double cost = c.n_layers * gate * 2 + head / 16;
+    if (best == 0 || cost < 0.97 * least) {
+      least = cost;
+      best = g;
+    }
+  }
+  return best;
 }
 // Bytes of one activation value: fp16 (bf16 weights), three bf16 parts (fp32 weights).
 inline size_t act_bytes(const zo_config& c) { return c.wdtype == ZO_WBF16 ? 2 : 6; }
@@ -304,13 +379,13 @@ inline WsPlan plan_workspace(const zo_config& c, const Rows& r, int32_t C) {
   return w;
 }
 
-// What zo_perturbed_losses_noalloc holds against its fixed size. fp32 weights:
-// a fixed account of a call's needs (4 bytes per activation, chunks of
-// kTimeChunk, batches padded to 32 or 64 sequences), so that the shapes it
-// takes do not depend on how the forward lays out its buffers; a workspace
-// takes at most 1.5 times it.
+// What zo_perturbed_losses_noalloc holds against its fixed size: a fixed
+// account of a call's needs (batches padded to 128 or 256 sequences with bf16
+// weights, to 32 or 64 with fp32 ones, there also 4 bytes per activation and
+// chunks of kTimeChunk), so that the shapes it takes do not depend on how the
+// forward lays out its buffers; a workspace takes at most 1.5 times it.
 inline size_t noalloc_account(const zo_config& c, int32_t N, int32_t B, int32_t C, bool fd) {
-  if (c.wdtype == ZO_WBF16) return plan_workspace(c, make_rows(N, B, row_granule(c, fd), fd), C).min_total;
+  if (c.wdtype == ZO_WBF16) return plan_workspace(c, make_rows(N, B, fd ? 256 : 128, fd), C).min_total;
   const size_t M = (size_t)make_rows(N, B, fd ? 64 : 32, fd).M, T = (size_t)(C < kTimeChunk ? C : kTimeChunk);
   const size_t E = (size_t)c.embed, H = (size_t)c.hidden, V = (size_t)c.vocab, L = (size_t)c.n_layers;
   const size_t nvt = (V + kVocabTile - 1) / kVocabTile;

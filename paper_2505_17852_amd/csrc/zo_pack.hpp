@@ -83,14 +83,17 @@ __host__ __device__ inline uint64_t act_copy_offset(int q, int w, int lane, int 
 // sign of parameter j (32 per word).
 __host__ __device__ inline uint32_t sign_word_offset(uint64_t j) { return (uint32_t)(j >> 5) * 4u; }
 
-// The gate's cell-state tile (the workgroup's 256 rows x 64 hidden units,
-// fp32, row stride H in global memory, 256 bytes per row in LDS): 64 copies
-// of 1 KB, 4 rows each; lane L of copy cp writes row 4 cp + L / 16, units
-// u0 + 4 (L % 16) .. + 3, at LDS byte 1024 cp + 16 L. Byte offset from the
-// tile's first row:
-__host__ __device__ inline int cell_row_of_copy(int cp, int lane) { return 4 * cp + (lane >> 4); }
-__host__ __device__ inline uint32_t cell_copy_offset(int cp, int lane, int64_t H, int64_t u0) {
-  return ((uint32_t)cell_row_of_copy(cp, lane) * (uint32_t)H + (uint32_t)u0) * 4u + 16u * (uint32_t)(lane & 15);
+// The gate's cell-state tile (the workgroup's rows x `cols` hidden units, 64
+// or 32, fp32, row stride H in global memory, 4 cols bytes per row in LDS):
+// copies of 1 KB, 256 / cols rows each; lane L of copy cp writes row (256 /
+// cols) cp + L / (cols / 4), units u0 + 4 (L % (cols / 4)) .. + 3, at LDS byte
+// 1024 cp + 16 L. Byte offset from the tile's first row:
+__host__ __device__ inline int cell_row_of_copy(int cp, int lane, int cols = 64) {
+  return 256 / cols * cp + lane / (cols / 4);
+}
+__host__ __device__ inline uint32_t cell_copy_offset(int cp, int lane, int64_t H, int64_t u0, int cols = 64) {
+  return ((uint32_t)cell_row_of_copy(cp, lane, cols) * (uint32_t)H + (uint32_t)u0) * 4u +
+         16u * (uint32_t)(lane % (cols / 4));
 }
 
 // The head's bias values of vocabulary tile v0 .. v0 + 255: the bias probe

@@ -12,7 +12,7 @@
 // Box-Muller pair and the initial-weight scaling) are a fixed contract: every
 // operation is a single correctly rounded fp32 operation, so that every
 // implementation of the contract yields the same bits. HIP compiles with
-// floating-point contraction on by default; the helpers fmul/fadd/fdiv turn
+// floating-point contraction on by default; the helpers fmul/fadd turn
 // it off (a multiply followed by an add must not become one fma).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -84,9 +84,7 @@ __device__ __forceinline__ uint32_t rademacher_word(Key key, uint32_t i, uint64_
 // ---- fixed fp32 sequences ------------------------------------------------
 
 // Single rounded operations. The contraction pragma sits inside each helper
-// (an fma can only form when both the multiply and the add allow it), and
-// sqrt / division use the compiler's correctly rounded expansions
-// (__fsqrt_rn would map to the 1-ulp hardware square root).
+// (an fma can only form when both the multiply and the add allow it).
 __device__ __forceinline__ float fmul(float a, float b) {
 #pragma clang fp contract(off)
   return a * b;
@@ -95,26 +93,39 @@ __device__ __forceinline__ float fadd(float a, float b) {
 #pragma clang fp contract(off)
   return a + b;
 }
-__device__ __forceinline__ float fdiv(float a, float b) {
-#pragma clang fp contract(off)
-  return a / b;
+// Correctly rounded n / d for the ratios of ln_pos (d in [1.7, 2.42], |n| < 0.42, n =
+// 0 or |n| >= 2^-24): the reciprocal with one Newton step, then the quotient
+// corrected by its exact remainder (Markstein, 1990). The range needs none of
+// the general division's scaling and special cases. Checked against the
+// correctly rounded quotient over every input the transform can meet.
+__device__ __forceinline__ float ratio(float n, float d) {
+  float r = __builtin_amdgcn_rcpf(d);
+  r = fmaf(fmaf(-d, r, 1.0f), r, r);
+  const float q = fmul(n, r);
+  return fmaf(fmaf(-d, q, n), r, q);
 }
-__device__ __forceinline__ float fsqrt(float a) { return __builtin_sqrtf(a); }
+// Correctly rounded square root of a = 0 (either sign, returned as it is) or
+// 2^-24 <= a < 64, from the hardware's reciprocal square root and one step on
+// the exact remainder; checked like ratio.
+__device__ __forceinline__ float sqrt_small(float a) {
+  const float r = __builtin_amdgcn_rsqf(a);
+  const float g = fmul(a, r), h = fmul(r, 0.5f);
+  const float y = fmaf(fmaf(-g, g, a), h, g);
+  return a == 0.0f ? a : y;
+}
 
-// Natural log of a normal float u in (0, 1]. Write u = 2^e m with m folded
-// into (sqrt(1/2), sqrt(2)]; then ln m = 2 atanh(s) with s = (m-1)/(m+1),
-// summed as s * (2 + s^2 (2/3 + s^2 (2/5 + s^2 (2/7 + s^2 2/9)))), and
-// ln u = e ln2_hi + (e ln2_lo + ln m) with ln 2 split into a 16-bit head and
-// its remainder.
-__device__ __forceinline__ float ln_u(float u) {
-  const uint32_t bits = __float_as_uint(u);
-  int e = (int)((bits >> 23) & 0xFFu) - 127;
-  float m = __uint_as_float((bits & 0x007FFFFFu) | 0x3F800000u);
-  if (m > __uint_as_float(0x3FB504F3u)) {  // largest float <= sqrt(2)
-    m = fmul(m, 0.5f);
-    e += 1;
-  }
-  const float s = fdiv(fadd(m, -1.0f), fadd(m, 1.0f));
+// Natural log of v 2^-24, v a positive normal float. Write v = 2^k m with m
+// folded into (sqrt(1/2), sqrt(2)] (the largest m that is not halved is
+// 0x3FB504F3, the largest float <= sqrt(2); adding and subtracting the bits of
+// half its successor moves k's carry to that place); then ln m = 2 atanh(s)
+// with s = (m-1)/(m+1), summed as s * (2 + s^2 (2/3 + s^2 (2/5 + s^2 (2/7 +
+// s^2 2/9)))), and ln u = e ln2_hi + (e ln2_lo + ln m), e = k - 24, with ln 2
+// split into a 16-bit head and its remainder.
+__device__ __forceinline__ float ln_pos(float v) {
+  const int32_t x = (int32_t)(__float_as_uint(v) - 0x3F3504F4u);
+  const int e = (x >> 23) - 24;
+  const float m = __uint_as_float(((uint32_t)x & 0x007FFFFFu) + 0x3F3504F4u);
+  const float s = ratio(fadd(m, -1.0f), fadd(m, 1.0f));
   const float s2 = fmul(s, s);
   float p = (float)(2.0 / 9.0);
   p = fadd(fmul(p, s2), (float)(2.0 / 7.0));
@@ -131,15 +142,16 @@ __device__ __forceinline__ float ln_u(float u) {
 
 // sin and cos of 2 pi k / 2^24 for a 24-bit integer k. Exact integer split
 // into the nearest quarter turn q and a remainder d in [-1/2, 1/2) quarter
-// turns; phi = d pi/2 in [-pi/4, pi/4); odd Taylor series of sin through
-// phi^9 and even series of cos through phi^10, then rotation by q.
+// turns; phi = d pi/2 in [-pi/4, pi/4) (one rounding: d = dk 2^-22 is exact,
+// so its power of two goes into the constant); odd Taylor series of sin
+// through phi^9 and even series of cos through phi^10, then rotation by q:
+// odd quarters swap the two, quarters 2 and 3 negate the sine, 1 and 2 the
+// cosine.
 __device__ __forceinline__ void sincos_turn24(uint32_t k24, float& s_out, float& c_out) {
   const int32_t k = (int32_t)(k24 & 0xFFFFFFu);
-  const int32_t qn = (k + (1 << 21)) >> 22;
-  const int32_t dk = k - (qn << 22);
-  const int q = qn & 3;
-  const float d = fmul((float)dk, __uint_as_float(0x34800000u));  // 2^-22, exact
-  const float phi = fmul(d, (float)1.57079632679489661923);
+  const uint32_t qn = (uint32_t)(k + (1 << 21)) >> 22;
+  const int32_t dk = k - (int32_t)(qn << 22);
+  const float phi = fmul((float)dk, (float)1.57079632679489661923 * 0x1p-22f);
   const float p2 = fmul(phi, phi);
   float sp = (float)(1.0 / 362880.0);
   sp = fadd(fmul(sp, p2), (float)(-1.0 / 5040.0));
@@ -154,19 +166,16 @@ __device__ __forceinline__ void sincos_turn24(uint32_t k24, float& s_out, float&
   cp = fadd(fmul(cp, p2), -0.5f);
   cp = fmul(cp, p2);
   const float cs = fadd(1.0f, cp);
-  switch (q) {
-    case 0: s_out = sn;  c_out = cs;  break;
-    case 1: s_out = cs;  c_out = -sn; break;
-    case 2: s_out = -sn; c_out = -cs; break;
-    default: s_out = -cs; c_out = sn; break;
-  }
+  const bool odd = (qn & 1u) != 0;
+  const uint32_t sv = __float_as_uint(odd ? cs : sn), cv = __float_as_uint(odd ? sn : cs);
+  s_out = __uint_as_float(sv ^ ((qn << 30) & 0x80000000u));
+  c_out = __uint_as_float(cv ^ (((qn + 1u) << 30) & 0x80000000u));
 }
 
 // Box-Muller (1958) on two words: u1 = (x0>>8 + 1) 2^-24 in (0, 1],
 // angle x1>>8 of 2^24; returns (r cos, r sin) with r = sqrt(-2 ln u1).
 __device__ __forceinline__ void gauss_pair(uint32_t x0, uint32_t x1, float& z0, float& z1) {
-  const float u1 = fmul((float)((x0 >> 8) + 1u), __uint_as_float(0x33800000u));  // 2^-24
-  const float r = fsqrt(fmul(-2.0f, ln_u(u1)));
+  const float r = sqrt_small(fmul(-2.0f, ln_pos((float)((x0 >> 8) + 1u))));
   float s, c;
   sincos_turn24(x1 >> 8, s, c);
   z0 = fmul(r, c);

@@ -189,33 +189,39 @@ __global__ __launch_bounds__(256) void reduce_kernel(const double* row_loss, int
   }
 }
 
-// Probe cache fill of the fp32 path: eps z of every weight matrix for probes
-// i0 .. i0+N-1 (layout: ZCacheMap, row-major matrices). The values are the
-// ones the forward kernels compute when they regenerate the probe,
-// fp32(eps * z) of the same normal value z. One thread per Philox block (4
-// values); the matrices are listed by their start in a probe's block and in
-// theta.
-struct ZSegs {
+// The fp32 path's product matrices, packed (row_piece), for the gate and head
+// kernels: in place their rows lie K values apart, a wave instruction's 64
+// lanes fall on 16 rows, and the address unit takes them one row at a time.
+// kProbe: instead of the weights, probes i0 .. i0 + N - 1's cached eps z
+// (ZCacheMap), the values the kernels compute when they regenerate the
+// probe, fp32(eps * z). One thread per 16-byte piece (one
+// Philox block).
+struct RowSegs {
   int n;
-  uint64_t cstart[2 * kMaxLayers + 2];  // start of matrix m in a probe's block; cstart[n] = P_g
+  uint64_t cstart[2 * kMaxLayers + 2];  // start of matrix m in a block of P_g values; cstart[n] = P_g
   uint64_t toff[2 * kMaxLayers + 1];    // offset of matrix m in theta
+  int64_t rows[2 * kMaxLayers + 1], K[2 * kMaxLayers + 1];
 };
 
-__global__ __launch_bounds__(256) void zcache_fill_kernel(float* zc, ZSegs segs, Key key, uint32_t i0, int N,
-                                                          float eps) {
+template <bool kProbe>
+__global__ __launch_bounds__(256) void row_pack_kernel(const float* theta, float* out, RowSegs segs, Key key,
+                                                       uint32_t i0, int N, float eps) {
   const uint64_t pg = segs.cstart[segs.n];
-  const uint64_t nb = pg >> 2;
+  const uint64_t np = pg >> 2;
   for (int n = blockIdx.y; n < N; n += gridDim.y) {
-    float* zp = zc + (uint64_t)n * pg;
-    for (uint64_t b = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nb;
-         b += (uint64_t)gridDim.x * blockDim.x) {
-      const uint64_t u = b << 2;
+    float* dst = out + (uint64_t)n * pg;
+    for (uint64_t u = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; u < np; u += (uint64_t)gridDim.x * blockDim.x) {
       int m = 0;
-      while (m + 1 < segs.n && u >= segs.cstart[m + 1]) ++m;
-      const uint64_t j = segs.toff[m] + (u - segs.cstart[m]);
-      float z[4];
-      gauss_block(key, i0 + (uint32_t)n, j >> 2, z);
-      *(f4*)(zp + u) = f4{fmul(eps, z[0]), fmul(eps, z[1]), fmul(eps, z[2]), fmul(eps, z[3])};
+      while (m + 1 < segs.n && 4 * u >= segs.cstart[m + 1]) ++m;
+      const RowPiece rp = row_piece(u - (segs.cstart[m] >> 2), segs.rows[m], segs.K[m]);
+      const uint64_t j = segs.toff[m] + (uint64_t)rp.row * (uint64_t)segs.K[m] + (uint64_t)rp.k;
+      if constexpr (kProbe) {
+        float z[4];
+        gauss_block(key, i0 + (uint32_t)n, j >> 2, z);
+        *(f4*)(dst + 4 * u) = f4{fmul(eps, z[0]), fmul(eps, z[1]), fmul(eps, z[2]), fmul(eps, z[3])};
+      } else {
+        *(f4*)(dst + 4 * u) = *(const f4*)(theta + j);
+      }
     }
   }
 }
@@ -327,20 +333,22 @@ __global__ __launch_bounds__(256) void zcache_pack_kernel(uint16_t* zc, const ui
 
 namespace {
 
-// The product matrices in theta order: their start in a probe-cache block
-// (fp32 path) and in theta.
-ZSegs matrix_segments(const ForwardArgs& a) {
+// The product matrices in theta order (fp32 path).
+RowSegs matrix_segments(const ForwardArgs& a) {
   const zo_config& c = a.cfg;
-  ZSegs segs{};
+  RowSegs segs{};
   int m = 0;
+  auto add = [&](uint64_t cstart, uint64_t toff, int64_t rows, int64_t K) {
+    segs.cstart[m] = cstart;
+    segs.toff[m] = toff;
+    segs.rows[m] = rows;
+    segs.K[m++] = K;
+  };
   for (int l = 0; l < c.n_layers; ++l) {
-    segs.cstart[m] = a.zmap.ih[l];
-    segs.toff[m++] = a.lay.w_ih[l];
-    segs.cstart[m] = a.zmap.hh[l];
-    segs.toff[m++] = a.lay.w_hh[l];
+    add(a.zmap.ih[l], a.lay.w_ih[l], 4 * (int64_t)c.hidden, l == 0 ? c.embed : c.hidden);
+    add(a.zmap.hh[l], a.lay.w_hh[l], 4 * (int64_t)c.hidden, c.hidden);
   }
-  segs.cstart[m] = a.zmap.out;
-  segs.toff[m++] = a.lay.w_out;
+  add(a.zmap.out, a.lay.w_out, c.vocab, c.hidden);
   segs.n = m;
   segs.cstart[m] = a.zmap.pg;
   return segs;
@@ -382,6 +390,15 @@ hipError_t launch_w16_fill(const ForwardArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// The fp32 path's packed weight copy.
+hipError_t launch_wpack(const ForwardArgs& a, hipStream_t st) {
+  const uint64_t grid = std::min<uint64_t>((a.zmap.pg / 4 + 255) / 256, 16384);
+  ProfScope ps(kKWeights16, st);
+  row_pack_kernel<false><<<dim3((unsigned)grid), 256, 0, st>>>((const float*)a.theta, const_cast<float*>(a.wpack),
+                                                               matrix_segments(a), Key{}, 0, 1, 0.f);
+  return hipGetLastError();
+}
+
 hipError_t launch_zcache_fill(const ForwardArgs& a, hipStream_t st) {
   const zo_config& c = a.cfg;
   const unsigned gy = (unsigned)(a.rows.N < 65535 ? a.rows.N : 65535);
@@ -395,10 +412,10 @@ hipError_t launch_zcache_fill(const ForwardArgs& a, hipStream_t st) {
     zcache_pack_kernel<<<dim3((unsigned)gx, gy), 256, 0, st>>>((uint16_t*)a.zc, (const uint16_t*)a.w16, segs, key,
                                                                 a.i0, a.rows.N, a.eps, !a.split);
   } else {
-    const ZSegs segs = matrix_segments(a);
     uint64_t gx = (a.zmap.pg / 4 + 255) / 256;
     if (gx > 4096) gx = 4096;
-    zcache_fill_kernel<<<dim3((unsigned)gx, gy), 256, 0, st>>>((float*)a.zc, segs, key, a.i0, a.rows.N, a.eps);
+    row_pack_kernel<true><<<dim3((unsigned)gx, gy), 256, 0, st>>>((const float*)a.theta, (float*)a.zc, matrix_segments(a),
+                                                                  key, a.i0, a.rows.N, a.eps);
   }
   return hipGetLastError();
 }
@@ -464,6 +481,7 @@ hipError_t launch_forward(const ForwardArgs& a, hipStream_t st) {
   // bf16 weights: the fp16 copy of the product matrices; probe cache (normal
   // probes, when the workspace holds it)
   if (bf16) ZO_TRY(launch_w16_fill(a, st));
+  if (a.wpack) ZO_TRY(launch_wpack(a, st));
   if (a.zc) ZO_TRY(launch_zcache_fill(a, st));
   if (a.bits) ZO_TRY(launch_bits_fill(a.bits, a.lay.total, a.seed, a.i0, R.N, st));
 
@@ -512,6 +530,8 @@ hipError_t launch_forward(const ForwardArgs& a, hipStream_t st) {
         g.off_hh = a.lay.w_hh[l];
         g.off_b = a.lay.bias[l];
         g.El = l == 0 ? c.embed : c.hidden;
+        g.w_ih = a.wpack ? a.wpack + a.zmap.ih[l] : (const float*)a.theta + g.off_ih;
+        g.w_hh = a.wpack ? a.wpack + a.zmap.hh[l] : (const float*)a.theta + g.off_hh;
         g.zb = zb + (size_t)l * R.N * 4 * H;
         g.zc_ih = a.zc ? (const float*)a.zc + a.zmap.ih[l] : nullptr;
         g.zc_hh = a.zc ? (const float*)a.zc + a.zmap.hh[l] : nullptr;

@@ -21,8 +21,11 @@
 //   the v_mfma_f32_16x16x32_bf16 operand. A workgroup copies the tiles of its
 //   rows into LDS (1 KB per wave instruction, linear, no bank conflicts), one
 //   stage of 8 (row tile, k tile) pairs ahead.
-// - Weights (and cached eps z of normal probes) are read in place, row-major
-//   fp32, 8 consecutive k per lane, PD k tiles ahead into registers. Each wave
+// - Weights (and cached eps z of normal probes) are read in fp32, 8
+//   consecutive k per lane, PD k tiles ahead into registers, from copies packed
+//   so that a wave instruction covers 1 KB of consecutive memory (row_piece;
+//   read in place the 64 lanes fall on 16 rows, which the address unit takes
+//   one by one: 256 normal probes of a 512-unit model 137 -> 117 ms). Each wave
 //   adds the probe term (w + eps z for the rows of the + pass, w - eps z for
 //   the - pass, one fp32 rounding) and splits the sum in registers: a
 //   workgroup's rows are RT row tiles of the + pass and the same RT tiles of
@@ -254,19 +257,21 @@ __device__ __forceinline__ void tile_of(int x, int total, int ncol, int& row, in
 // One K segment: packed activations, the weight matrix and its place in theta.
 struct Seg {
   const char* A;   // packed activations (K values per row), row tile 0
-  const float* W;  // row-major [rows][K]
+  const float* W;  // [rows][K], packed (row_piece) or row-major
   uint64_t zoff;   // offset of W inside theta (probe coordinates)
   int K;
-  const float* Z;  // kGaussCached: eps z of this probe and matrix, laid out like W
+  const float* Z;  // kGaussCached: eps z of this probe and matrix, packed
 };
 
 // acc[row tile][column tile] of this wave: 16x16 fp32, lane = column lane % 16,
-// rows 4 (lane / 16) + v. row0: the wave's first weight row (uniform); col(ct):
-// this lane's weight row of column tile ct, from row0. split: the two products W.h and (s eps z).h one after the other into
+// rows 4 (lane / 16) + v. rows: of the weight matrices; row0: the wave's first one
+// (uniform, a multiple of 16); col(ct): this lane's weight row of column tile
+// ct, from row0. split: the two products W.h and (s eps z).h one after the other into
 // one accumulator (twice the matrix work, for measurement).
 template <typename T, bool kSplit, typename Col, typename Init>
 __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0, const Seg s1, int nseg,
-                                         const RowTiles& rt, int row0, Col col, Key key, uint32_t probe, float eps,
+                                         const RowTiles& rt, int rows, int row0, Col col, bool packed, Key key,
+                                         uint32_t probe, float eps,
                                          const uint32_t* bits, uint8_t* st0, uint8_t* st1, Init init) {
   constexpr int NS = T::NS, RT = T::RT, CT = T::CT, S = T::S, NB = T::NB, PD = T::PD;
   const int lane = threadIdx.x & 63;
@@ -281,23 +286,42 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
     int g;
   };
   Buf buf[NB];
-  // Addresses of the weights: per segment the wave's first row (uniform) and
-  // this lane's byte offset from it (its row of column tile c and its 8 k, 32
-  // rows of K fp32 values at most); the k tile adds 128 bytes. Sign words: 32
-  // values per 4-byte word (K is a multiple of 32).
-  int rel[CT];
-  uint32_t lo[2][CT], lw[2][CT];
+  // Addresses of the weights. Packed, a wave's column tile c is one block of R
+  // rows (16; fewer at the end of the head matrix), a k tile of it 128 R
+  // consecutive bytes: two halves of 64 R, this lane's piece at (kg R + row)
+  // 16. In place (a workspace without the packed copy), this lane's row with
+  // 128 bytes per k tile, its halves 16 bytes apart. Sign words: 32 values per
+  // 4-byte word (K is a multiple of 32).
+  int rel[CT];               // this lane's row of column tile c, from row0
+  uint32_t lp[CT], tp[CT];   // packed: lane offset, bytes per k tile
+  uint32_t lw[2][CT];
+  int64_t blk[CT];           // first row of column tile c's block
+  uint32_t lo[2][CT];        // in place: lane offset from the block
 #pragma unroll
   for (int c = 0; c < CT; ++c) {
     rel[c] = col(c);
-    lo[0][c] = (uint32_t)(rel[c] * s0.K + 8 * kg) * 4u;
-    lo[1][c] = (uint32_t)(rel[c] * s1.K + 8 * kg) * 4u;
+    const int b0 = min(16 * c, (rows - 1 - row0) & ~15);  // column tiles past the matrix repeat its last block
+    const int R = min(16, rows - row0 - b0);
+    blk[c] = (int64_t)row0 + b0;
+    lp[c] = (uint32_t)((kg * R + rel[c] - b0) * 16);
+    tp[c] = (uint32_t)R * 128u;
+    lo[0][c] = (uint32_t)((rel[c] - b0) * s0.K + 8 * kg) * 4u;
+    lo[1][c] = (uint32_t)((rel[c] - b0) * s1.K + 8 * kg) * 4u;
     lw[0][c] = (uint32_t)(rel[c] * (s0.K >> 5)) * 4u;
     lw[1][c] = (uint32_t)(rel[c] * (s1.K >> 5)) * 4u;
   }
   const int64_t r0 = (int64_t)row0 * s0.K, r1 = (int64_t)row0 * s1.K;
-  const char* wbase[2] = {(const char*)(s0.W + r0), (const char*)(s1.W + r1)};
-  const char* zbase[2] = {(const char*)(s0.Z + r0), (const char*)(s1.Z + r1)};
+  const char* wbase[2][CT];
+  const char* zbase[2][T::kZ ? CT : 1];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    wbase[0][c] = (const char*)(s0.W + blk[c] * s0.K);
+    wbase[1][c] = (const char*)(s1.W + blk[c] * s1.K);
+    if constexpr (T::kZ) {
+      zbase[0][c] = (const char*)(s0.Z + blk[c] * s0.K);
+      zbase[1][c] = (const char*)(s1.Z + blk[c] * s1.K);
+    }
+  }
   const char* bbase[2] = {(const char*)(bits + ((s0.zoff + (uint64_t)r0) >> 5)),
                           (const char*)(bits + ((s1.zoff + (uint64_t)r1) >> 5))};
   // weights (and probe values or sign words) of k tile g, the last tile past the end
@@ -305,18 +329,18 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
     g = min(g, ntiles - 1);
     const bool second = g >= kt0;
     const uint32_t kt = (uint32_t)(second ? g - kt0 : g);
-    const char* W = (second ? wbase[1] : wbase[0]) + kt * 128u;
-    const char* Z = (second ? zbase[1] : zbase[0]) + kt * 128u;
     const char* wd = (second ? bbase[1] : bbase[0]) + kt * 4u;
     b.g = g;
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
-      const uint32_t v = second ? lo[1][c] : lo[0][c];
+      const char* W = (second ? wbase[1][c] : wbase[0][c]) + kt * (packed ? tp[c] : 128u);
+      const uint32_t v = packed ? lp[c] : second ? lo[1][c] : lo[0][c];
       b.w[c][0] = *(const f4*)(W + v);
-      b.w[c][1] = *(const f4*)(W + v + 16);
+      b.w[c][1] = *(const f4*)(W + (packed ? tp[c] / 2 : 16u) + v);
       if constexpr (T::kZ) {
-        b.z[c][0] = *(const f4*)(Z + v);
-        b.z[c][1] = *(const f4*)(Z + v + 16);
+        const char* Z = (second ? zbase[1][c] : zbase[0][c]) + kt * tp[c];
+        b.z[c][0] = *(const f4*)(Z + lp[c]);
+        b.z[c][1] = *(const f4*)(Z + tp[c] / 2 + lp[c]);
       }
       if constexpr (T::kBits) b.word[c] = *(const uint32_t*)(wd + (second ? lw[1][c] : lw[0][c]));
     }
@@ -572,6 +596,7 @@ struct GateArgs {
   const uint32_t* bits;  // sign-probe cache: probe 0's words; probe n at + n * bits_stride
   uint64_t bits_stride;
   int ncol;              // column blocks
+  bool packed;           // the layers' weights are packed copies
 };
 
 template <typename T, bool kSplit>
@@ -609,11 +634,11 @@ __global__ __launch_bounds__(NT, 2) void gate_f32_kernel(GateArgs g) {
   }
   auto init = [&]() { bias_init<T>(acc, bias, zb, rt.sign0); };
   const uint64_t zpos = (uint64_t)rt.probe * g.zc_stride;
-  const Seg s0{gl.x, g.theta + gl.off_ih, gl.off_ih, gl.El, T::kZ ? gl.zc_ih + zpos : nullptr};
-  const Seg s1{gl.hprev, g.theta + gl.off_hh, gl.off_hh, H, T::kZ ? gl.zc_hh + zpos : nullptr};
+  const Seg s0{gl.x, gl.w_ih, gl.off_ih, gl.El, T::kZ ? gl.zc_ih + zpos : nullptr};
+  const Seg s1{gl.hprev, gl.w_hh, gl.off_hh, H, T::kZ ? gl.zc_hh + zpos : nullptr};
   mainloop<T, kSplit>(
-      acc, s0, s1, 2, rt, __builtin_amdgcn_readfirstlane(wave * H + u0), [&](int ct) { return 16 * ct + (lane & 15); }, g.key,
-      g.i0 + (uint32_t)rt.probe, g.eps, T::kBits ? g.bits + (uint64_t)rt.probe * g.bits_stride : nullptr, st0, st1, init);
+      acc, s0, s1, 2, rt, 4 * H, __builtin_amdgcn_readfirstlane(wave * H + u0),
+      [&](int ct) { return 16 * ct + (lane & 15); }, g.packed, g.key, g.i0 + (uint32_t)rt.probe, g.eps, T::kBits ? g.bits + (uint64_t)rt.probe * g.bits_stride : nullptr, st0, st1, init);
 #pragma unroll
   for (int c = 0; c < RTT / 2; ++c) {
     float* ep = (float*)(c & 1 ? st1 : st0);
@@ -671,6 +696,8 @@ struct HeadArgs {
   int64_t rows;    // Tc M
   int blocks_per_t;  // row blocks of one timestep
   int nvt;             // vocabulary tiles
+  const float* w_out;  // W_out: packed copy, or theta's own
+  bool packed;
   const int32_t* tokens;
   int C, t0, B;
   float* pmax;  // [nvt][rows]
@@ -709,7 +736,7 @@ __global__ __launch_bounds__(NT, 2) void head_f32_kernel(HeadArgs g) {
     tgt[c] = b < g.B ? g.tokens[(int64_t)b * (g.C + 1) + g.t0 + tt + 1] - v0 : -1;
   }
   f4 acc[RTT][CT];
-  const int row0 = __builtin_amdgcn_readfirstlane(min(v0 + 16 * CT * wave, V - 1));
+  const int row0 = __builtin_amdgcn_readfirstlane(min(v0 + 16 * CT * wave, (V - 1) & ~15));
   auto col = [&](int ct) { return min(16 * ct + (lane & 15), V - 1 - row0); };
   float bias[CT], zb[CT];
 #pragma unroll
@@ -718,9 +745,9 @@ __global__ __launch_bounds__(NT, 2) void head_f32_kernel(HeadArgs g) {
     zb[ct] = g.zbo[(int64_t)rt.probe * V + row0 + col(ct)];
   }
   auto init = [&]() { bias_init<T>(acc, bias, zb, rt.sign0); };
-  const Seg s0{g.h, g.theta + g.off_w, g.off_w, g.H,
+  const Seg s0{g.h, g.w_out, g.off_w, g.H,
                T::kZ ? g.zc_out + (uint64_t)rt.probe * g.zc_stride : nullptr};
-  mainloop<T, kSplit>(acc, s0, s0, 1, rt, row0, col, g.key, g.i0 + (uint32_t)rt.probe, g.eps,
+  mainloop<T, kSplit>(acc, s0, s0, 1, rt, V, row0, col, g.packed, g.key, g.i0 + (uint32_t)rt.probe, g.eps,
                       T::kBits ? g.bits + (uint64_t)rt.probe * g.bits_stride : nullptr, st0, st1, init);
 #pragma unroll
   for (int c = 0; c < RTT / 2; ++c) {
@@ -834,6 +861,7 @@ hipError_t launch_gates_f32(const ForwardArgs& a, const GateLayerF32* ls, int n,
   const int ns = R.fd ? 1 : 2;
   const Pick pk = pick_shape(g.rm, R.M, ns, 4 * (int64_t)g.H, n, !a.split);
   g.ncol = g.H / (16 * pk.ct);
+  g.packed = a.wpack != nullptr;
   const int64_t blocks = row_blocks(g.rm, R.M, ns, pk.rt) * g.ncol;
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks, (unsigned)n);
@@ -883,6 +911,8 @@ hipError_t launch_head_f32(const ForwardArgs& a, const void* hist, int t0, int T
   const Pick pk = pick_shape(h.rm, R.M, ns, (int64_t)a.ws.nvt * kVocabTile, Tc, false);
   h.blocks_per_t = (int)row_blocks(h.rm, R.M, ns, pk.rt);
   h.nvt = a.ws.nvt;
+  h.packed = a.wpack != nullptr;
+  h.w_out = a.wpack ? a.wpack + a.zmap.out : (const float*)a.theta + a.lay.w_out;
   const int64_t blocks = (int64_t)h.blocks_per_t * Tc * h.nvt;
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks);

@@ -144,7 +144,8 @@ static int forward_call(const zo_config* cfg, const void* theta, uint64_t seed, 
   const zo::Rows rows = zo::make_rows(N, B, zo::row_granule(*cfg, N, B, fd), fd);
   if (rows.M > (int64_t)1 << 30) return fail(ZO_ESHAPE, "rows of all passes too many");
   const zo::WsPlan plan = zo::plan_workspace(*cfg, rows, C);
-  // regen: the fixed scratch may lack room for the fp32 path's sign words
+  // regen: the fixed scratch may lack room for the fp32 path's packed weights
+  // and sign words (the kernels then read theta itself and regenerate them)
   const size_t need = regen ? plan.regen_total : plan.min_total;
   if (ws_bytes < need) return fail(ZO_ENOMEM, "workspace of %zu bytes < %zu required", ws_bytes, need);
   zo::ForwardArgs a;
@@ -170,6 +171,11 @@ static int forward_call(const zo_config* cfg, const void* theta, uint64_t seed, 
     a.split = products == ZO_PRODUCTS_SPLIT;
   // the probe cache is used when the workspace has room for it
   a.zc = (zo::probe_cache_kind(*cfg) && ws_bytes >= plan.total) ? (char*)workspace + plan.zcache : nullptr;
+  // the packed weight copy: one launch more, made up for after a few hundred k
+  // tiles per column (c1, 96 of them: 232 us per step without it, 238 with;
+  // c2's evaluation, 3,600: 2.75 against 2.62 ms)
+  const bool pack = (int64_t)C * (cfg->embed + cfg->hidden) / 32 >= 256 && ws_bytes >= plan.min_total;
+  a.wpack = cfg->wdtype == ZO_WFP32 && pack ? (const float*)((char*)workspace + plan.wpack) : nullptr;
   // the sign words: always with fp32 weights (min_total holds them), with bf16
   // weights when the workspace has room for them (total does)
   a.bits = cfg->probe == ZO_RADEMACHER && ws_bytes >= (cfg->wdtype == ZO_WFP32 ? plan.min_total : plan.total)

@@ -215,8 +215,8 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // kernels would otherwise regenerate: eps z in fp32 (fp32 weights) or
 // fp16(eps z) (bf16 weights), for probes i0 .. i0+N-1. Layout: probe n's
 // block of P_g values (the matrices in theta order) at n * P_g; each matrix
-// row-major like the matrix itself (fp32 weights) or fragment-packed like the
-// fp16 weight copy (bf16 weights, zo_pack.hpp). Sign probes are cheap to
+// packed like the weight copy the kernels read: row_piece (fp32 weights) or
+// fragment-packed fp16 (bf16 weights), both in zo_pack.hpp. Sign probes are cheap to
 // regenerate and are never cached. The same map places the matrices of the
 // bf16 path's fp16 weight copy; there the head matrix is padded with zero
 // rows to a whole number of 256-wide vocabulary tiles.
@@ -315,7 +315,9 @@ struct WsPlan {
   size_t row_loss;   // f64 [M]            masked loss sum of each row
   size_t w16;        // f16 [P_g]          bf16 weights: the product matrices in fp16 (ZCacheMap layout)
   size_t regen_total;  // bytes with which the forward can run at all (every probe regenerated in every tile)
-  size_t min_total;  // bytes the entry points ask for at least: as above, and the fp32 path's sign words
+  size_t wpack;      // f32 [P_g]          fp32 weights: the product matrices packed (row_piece)
+  size_t min_total;  // bytes the entry points ask for at least: as above, and the fp32 path's packed
+                     // weights and sign words
   size_t zcache;     // probe cache (normal probes; see ZCacheMap): fp32 weights [N][P_g] eps z;
                      // bf16 weights [N][2][P_g] fp16: probe n's perturbed weights
                      // fp16(w + fp16(eps z)) and fp16(w - fp16(eps z)) (fused products), or
@@ -364,6 +366,8 @@ inline WsPlan plan_workspace(const zo_config& c, const Rows& r, int32_t C) {
   w.w16 = p;
   if (c.wdtype == ZO_WBF16) take((size_t)make_zcache_map(c).pg * 2);
   w.regen_total = p;
+  w.wpack = p;
+  if (c.wdtype == ZO_WFP32) take((size_t)make_zcache_map(c).pg * 4);
   const bool sign = c.probe == ZO_RADEMACHER;
   const size_t bits = sign ? (size_t)r.N * bit_words(make_layout(c).total) * 4 : 0;
   w.bits = p;

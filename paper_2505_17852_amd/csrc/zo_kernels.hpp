@@ -47,6 +47,8 @@ struct ForwardArgs {
   void* zc;         // probe cache inside work, or nullptr (probes regenerated in every tile)
   uint32_t* bits;   // sign-probe cache inside work (sign probes), or nullptr
   void* w16;        // bf16 weights: fp16 copy of the product matrices inside work (ZCacheMap layout)
+  const float* wpack;  // fp32 weights: the packed product matrices inside work (ZCacheMap layout), or nullptr
+                       // (read in place)
   ZCacheMap zmap;
 };
 hipError_t launch_forward(const ForwardArgs& a, hipStream_t s);
@@ -63,6 +65,8 @@ struct GateLayerF32 {
   float* cst;         // [M][H] fp32, row-major
   uint64_t off_ih, off_hh, off_b;
   int El;
+  const float* w_ih;   // W_ih and W_hh: packed copies, or theta's own
+  const float* w_hh;
   const float* zb;     // [N][4H] eps z of this layer's bias
   const float* zc_ih;  // probe cache: W_ih's and W_hh's values of probe 0; probe n at + n * zc_stride
   const float* zc_hh;

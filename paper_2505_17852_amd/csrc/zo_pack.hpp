@@ -123,4 +123,27 @@ __host__ __device__ inline size_t split_offset(int64_t rt, int row, int k, int K
   return (size_t)(rt * (K >> 5) + (k >> 5)) * (kSplitParts * 1024) + (size_t)((row + 16 * ((k & 31) >> 3)) * 16 + (k & 7) * 2);
 }
 
+// fp32 path: weight matrices (and cached eps z) packed in the order the gate and
+// head kernels read them, so that a wave instruction covers consecutive
+// memory: rows in blocks of 16 (the last block may have fewer, R), K in tiles
+// of 32; block b starts at value 16 b K and holds, per k tile, the 16-byte
+// pieces [half][kg][row] of the R rows: values k = 32 kt + 8 kg + 4 half .. + 3
+// of row 16 b + row. (rows, k) of 16-byte piece u of a matrix of n rows of K:
+struct RowPiece {
+  int64_t row;
+  int k;
+};
+__host__ __device__ inline int64_t block_rows(int64_t b, int64_t n) { return n - 16 * b < 16 ? n - 16 * b : 16; }
+__host__ __device__ inline RowPiece row_piece(uint64_t u, int64_t n, int64_t K) {
+  const int64_t b = (int64_t)(u / (uint64_t)(4 * K));  // 16 rows of K / 4 pieces
+  uint32_t rem = (uint32_t)(u - (uint64_t)b * (uint64_t)(4 * K));
+  const uint32_t R = (uint32_t)block_rows(b, n);
+  const uint32_t kt = rem / (8 * R);
+  rem -= kt * 8 * R;
+  const uint32_t half = rem / (4 * R);
+  rem -= half * 4 * R;
+  const uint32_t kg = rem / R;
+  return RowPiece{16 * b + (rem - kg * R), (int)(32 * kt + 8 * kg + 4 * half)};
+}
+
 }  // namespace zo

@@ -26,7 +26,8 @@ if ROOT not in sys.path:
 
 METRIC = "perturbed-forward tokens/sec per CD-RGE step (2N·B·C/s); % MFMA peak"
 METRIC_FD = "forward tokens/sec per FD-RGE step ((N+1)·B·C/s); % MFMA peak"
-PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0, "fp16": 2500.0}  # dense MFMA peaks of MI355X
+# Dense MFMA peaks of MI355X. fp32 products run as six bf16 products each (exactly split operands).
+PEAK_TFLOPS = {"f32": 2500.0 / 6, "bf16": 2500.0, "fp16": 2500.0}
 HBM_PEAK_GBPS = 8000.0  # HBM3E peak of MI355X
 DEFAULTS = {"c1": (3, 20), "c2": (3, 20), "c3": (1, 3), "c4": (1, 3), "c5": (1, 3)}
 # Event timing: every launch where kernels are long (an event pair adds a few µs to the
@@ -59,7 +60,8 @@ def kernel_source_hash(dtype):
     """Hash of the gate kernel's sources, to match the committed counter runs."""
     import hashlib
     src = os.path.join(ROOT, "paper_2505_17852_amd", "csrc")
-    files = (["k_forward_bf16.hip", "zo_pack.hpp"] if dtype == "bf16" else ["k_forward.hip"]) + ["zo_rng.hpp", "zo_common.hpp"]
+    files = ["k_forward_bf16.hip" if dtype == "bf16" else "k_forward_f32.hip", "zo_pack.hpp", "zo_cell.hpp",
+             "zo_rng.hpp", "zo_common.hpp"]
     m = hashlib.sha256()
     for f in files:
         with open(os.path.join(src, f), "rb") as fh:
@@ -130,16 +132,14 @@ def update_hbm(P, w, upd):
 
 def embed_hbm(cfg, passes, B, C, w, emb, launches_per_step, fd=False):
     """Algorithmic HBM rate of the perturbed-embedding kernel: per timestep it
-    writes the passes*B rows of E activations (w bytes each; padding rows
-    included, as written) and reads B rows of EMB; a launch covers one
-    timestep (bf16) or a time chunk (fp32)."""
+    writes the passes*B rows of E activations (fp16, or three bf16 parts with
+    fp32 weights) and reads B rows of EMB; a launch covers one timestep (bf16)
+    or a time chunk (fp32)."""
     ms, n = emb
     if n == 0 or ms <= 0 or not launches_per_step:
         return None
-    gran = (128 if w == 2 else 32) * (2 if fd else 1)
-    Bp = (B + gran - 1) // gran * gran
-    E = cfg["embed"]
-    byt = C * (passes * Bp * E * w + B * E * w) / launches_per_step
+    E, act = cfg["embed"], 2 if w == 2 else 6
+    byt = C * (passes * B * E * act + B * E * w) / launches_per_step
     gbps = byt / (ms / n * 1e-3) / 1e9
     return {"bytes_per_launch": byt, "ms_per_launch": ms / n, "GBps": gbps, "frac": gbps / HBM_PEAK_GBPS}
 
@@ -179,13 +179,11 @@ def head_hbm(cfg, passes, B, C, w, head, launches_per_step, fd=False):
     ms, n = head
     if n == 0 or ms <= 0 or not launches_per_step:
         return None
-    gran = (128 if w == 2 else 32) * (2 if fd else 1)
-    Bp = (B + gran - 1) // gran * gran
     V, H = cfg["vocab"], cfg["hidden"]
-    M = passes * Bp
+    M, act = passes * B, 2 if w == 2 else 6
     vt = 256 if w == 2 else 128
     nvt = (V + vt - 1) // vt
-    per_step = launches_per_step * V * H * w + C * M * H * w + C * M * (8 * nvt + 4)
+    per_step = launches_per_step * V * H * w + C * M * H * act + C * M * (8 * nvt + 4)
     byt = per_step / launches_per_step
     gbps = byt / (ms / n * 1e-3) / 1e9
     return {"bytes_per_launch": byt, "ms_per_launch": ms / n, "GBps": gbps, "frac": gbps / HBM_PEAK_GBPS}

@@ -105,8 +105,10 @@ typedef struct {
  * both forms. zo_perturbed_losses chooses by eps (ZO_PRODUCTS_AUTO); the _ex
  * entry points take the form as an argument, for measurement. A bf16 call
  * with eps < ZO_BF16_EPS_MIN returns ZO_EINVAL. fp32 weights form
- * w +- eps z in fp32 (fused, one fp32 rounding); their two-stream form exists
- * for measurement only (central differences). */
+ * w +- eps z in fp32 (fused, one fp32 rounding) and run each fp32 product as
+ * six bf16 products of the operands' three exact bf16 parts, accumulated in
+ * fp32 (a non-finite weight gives non-finite losses); their two-stream form
+ * exists for measurement only (central differences). */
 #define ZO_BF16_FUSED_EPS_MIN 0x1p-10f /* 9.765625e-4 */
 #define ZO_BF16_EPS_MIN 0x1p-17f       /* 7.62939453125e-6 */
 enum { ZO_PRODUCTS_AUTO = 0, ZO_PRODUCTS_FUSED = 1, ZO_PRODUCTS_SPLIT = 2 };
@@ -118,8 +120,9 @@ size_t zo_param_count(const zo_config* cfg);
 /* Bytes of device workspace zo_perturbed_losses (or zo_fd_losses) uses for N probes and a
  * batch of B sequences of C positions; 0 if the arguments are invalid.
  * Host only. With bf16 weights every workspace holds an fp16 copy of the
- * weight matrices (every W_ih, W_hh and W_out; P_g values), written once per
- * call. With normal probes this includes the probe cache, written once per
+ * weight matrices (every W_ih, W_hh and W_out; P_g values), with fp32 weights
+ * a packed fp32 copy and, for sign probes, the probes' sign words (N P / 8
+ * bytes), all written by the call. With normal probes this includes the probe cache, written once per
  * call and read by every timestep instead of regenerating the probe in every
  * tile (the results are bit-identical either way): N * P_g values of eps z
  * for fp32 weights; 2 * N * P_g fp16 values for bf16 weights, each probe's
@@ -166,9 +169,9 @@ int zo_init(const zo_config* cfg, void* theta, uint64_t seed, void* stream);
  *            (normal probes: at least zo_workspace_bytes() to use the probe
  *            cache; same results, fewer probe regenerations)
  * Returns ZO_OK, ZO_EINVAL, ZO_ESHAPE, ZO_ENOMEM or ZO_EDEVICE.
- * fp32 weights: each matrix product uses the perturbed weight tile
- * w +- eps z formed in LDS (one fp32 rounding). bf16 weights: the fused or
- * the two-stream products by eps (see "Products"). */
+ * fp32 weights: each matrix product uses the perturbed weights w +- eps z
+ * (one fp32 rounding). bf16 weights: the fused or the two-stream products by
+ * eps (see "Products"). */
 int zo_perturbed_losses(const zo_config* cfg, const void* theta, uint64_t seed, float eps,
                         int32_t N, uint32_t i0, const int32_t* tokens, const uint8_t* mask,
                         int32_t B, int32_t C, float* Lplus, float* Lminus, void* workspace,
@@ -186,12 +189,16 @@ int zo_perturbed_losses_ex(const zo_config* cfg, const void* theta, uint64_t see
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc):
  * zo_perturbed_losses without a workspace argument. The workspace is a fixed
- * device array of ZO_NOALLOC_WORKSPACE_BYTES inside the library, one per
- * device, held from the first call on that device until the process ends
- * (the probe cache is used when zo_workspace_bytes() fits in it as well).
- * The call allocates and frees nothing, and does no kernel timing. A shape
- * whose zo_workspace_bytes_min() exceeds the array returns ZO_ENOMEM before
- * anything is enqueued. Every call on a device shares that device's array:
+ * device array inside the library, one per device, held from the first call
+ * on that device until the process ends (caches and packed copies are used
+ * when they fit in it; the results are the same without). The call allocates
+ * and frees nothing, and does no kernel timing. A shape whose needs exceed
+ * ZO_NOALLOC_WORKSPACE_BYTES returns ZO_ENOMEM before anything is enqueued;
+ * they are counted by a fixed account (bf16 weights: batches padded to a
+ * multiple of 128, 256 for what forward differences would need; fp32 weights:
+ * 32 or 64, 4 bytes per activation, states of up to 16 timesteps), which
+ * zo_workspace_bytes_min() may be above or below; the array is half as large
+ * again. Every call on a device shares that device's array:
  * calls that overlap on one device (concurrent streams or threads) race and
  * must be serialised by the caller. Each call clears what it reads before
  * writing it, so no state carries from one call to the next. Other arguments,

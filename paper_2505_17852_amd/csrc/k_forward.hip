@@ -4,17 +4,15 @@
 // Every pass (probe n, sign s) runs the same LSTM on the same B sequences
 // with weights theta + s eps z_n. A matrix product of a timestep is computed
 // for all 2N*B rows at once as
-//     a[r] = sum_k A[r][k] W[c][k]  +  sum_k (s_r A[r][k]) (eps z_n[c][k])
-// i.e. the shared weights times the state plus the probe times the signed
-// state, accumulated in one MFMA accumulator. z_n is regenerated tile by
-// tile in LDS from (seed, n, parameter offset); theta + s eps z_n is never
-// formed in memory.
+//     a[r] = sum_k A[r][k] (W[c][k] + s_r eps z_n[c][k])
+// with the perturbed weight formed from the shared weight and the probe where
+// the kernel reads it; theta + s eps z_n as a whole is never formed in memory.
 //
 // Per timestep: embed (perturbed embedding rows) -> one gate kernel per
 // layer (both input products, bias, gate nonlinearities and the cell update
-// fused). Every kTimeChunk timesteps: one output-head kernel over the
-// chunk's top-layer states (vocabulary-tiled, online logsumexp partials),
-// then a combine kernel that adds each position's cross-entropy to its row.
+// fused). Every time chunk: one output-head kernel over the chunk's top-layer
+// states (vocabulary-tiled, online logsumexp partials), then a combine kernel
+// that adds each position's cross-entropy to its row.
 // At the end a reduction turns row sums into the 2N losses.
 #include <hip/hip_runtime.h>
 

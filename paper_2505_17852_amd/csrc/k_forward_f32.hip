@@ -34,7 +34,7 @@
 //
 // Measured against v_mfma_f32_16x16x4_f32 on the same rows (64 x 128 and 128 x
 // 128 tiles through LDS): the two-layer gate launch of a 256-unit model with
-// 4,096 rows 83.8 -> 51 us, with 128 rows 36 -> 11.5 us; losses against 64 bits
+// 4,096 rows 83.8 -> 47.5 us, with 128 rows 36 -> 10 us; losses against 64 bits
 // with weights scaled up until the products' own error shows: 2.1e-7 against
 // 2.9e-7, 2.2e-7 against 3.0e-7, 2.6e-7 against 3.5e-7 (three models).
 //

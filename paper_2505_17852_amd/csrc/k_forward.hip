@@ -465,8 +465,8 @@ hipError_t launch_forward(const ForwardArgs& a, hipStream_t st) {
     zr.n_slots = L - 1;
     zr.n_state = (int64_t)(state / 16);
     zr.stride = 2 * zr.n_state;
-    zr.p[0] = (uint4*)(hist + (size_t)(T - 1) * state);
-    zr.n[0] = zr.n_state;
+    zr.p[0] = (uint4*)(T > 1 ? hist + (size_t)(T - 1) * state : ws + W.hzero);
+    zr.n[0] = T > 1 ? zr.n_state : (int64_t)(zero_state_bytes(c) / 16);
     zr.p[1] = (uint4*)cbuf;
     zr.n[1] = (int64_t)((size_t)L * M * H / 4);
     zr.p[2] = (uint4*)row_loss;
@@ -488,10 +488,12 @@ hipError_t launch_forward(const ForwardArgs& a, hipStream_t st) {
   if (a.bits) ZO_TRY(launch_bits_fill(a.bits, a.lay.total, a.seed, a.i0, R.N, st));
 
   // states of layer l at time t: lower layers alternate between two slots
-  // (time t in slot t & 1), the top layer writes the time-chunk ring
+  // (time t in slot t & 1), the top layer writes the time-chunk ring. A ring of
+  // one slot (C = 1) holds only the state being written, while other
+  // workgroups still read the one before it: that one is a zero row of its own
   auto state_in = [&](int l, int t) -> char* {  // h of layer l at time t - 1
     if (l < L - 1) return hbuf + (size_t)l * 2 * state + (size_t)((t + 1) & 1) * state;
-    return hist + (size_t)((t + T - 1) % T) * state;
+    return T > 1 ? hist + (size_t)((t + T - 1) % T) * state : ws + W.hzero;
   };
   auto state_out = [&](int l, int t) -> char* {  // h of layer l at time t
     if (l < L - 1) return hbuf + (size_t)l * 2 * state + (size_t)(t & 1) * state;
@@ -526,6 +528,7 @@ hipError_t launch_forward(const ForwardArgs& a, hipStream_t st) {
         GateLayerF32& g = ls[n++];
         g.x = l == 0 ? x0 + (size_t)(t % T) * x0_step : state_out(l - 1, t);
         g.hprev = state_in(l, t);
+        g.hstep = l == L - 1 && T == 1 ? 0 : (int64_t)(16 * (size_t)H * el);
         g.hout = state_out(l, t);
         g.cst = cbuf + (size_t)l * M * H;
         g.off_ih = a.lay.w_ih[l];

@@ -257,6 +257,7 @@ __device__ __forceinline__ void tile_of(int x, int total, int ncol, int& row, in
 // One K segment: packed activations, the weight matrix and its place in theta.
 struct Seg {
   const char* A;   // packed activations (K values per row), row tile 0
+  int64_t step;    // bytes between row tiles: K / 32 kFrag, or 0 (one tile for all rows)
   const float* W;  // [rows][K], packed (row_piece) or row-major
   uint64_t zoff;   // offset of W inside theta (probe coordinates)
   int K;
@@ -358,12 +359,13 @@ __device__ __forceinline__ void mainloop(f4 (&acc)[T::RTT][T::CT], const Seg s0,
     const int last = h ? rt.last1 : rt.last0;
     const int64_t first = (h ? rt.base1 : rt.base0) + min(0, last);
     const uint32_t i = (uint32_t)min(min(wave / S, RT - 1), max(0, last));
-    abase[0][h] = s0.A + first * kt0 * kFrag;
-    abase[1][h] = s1.A + first * (s1.K >> 5) * kFrag;
-    co[0][h] = i * (uint32_t)kt0 * kFrag;
-    co[1][h] = i * (uint32_t)(s1.K >> 5) * kFrag;
+    abase[0][h] = s0.A + first * s0.step;
+    abase[1][h] = s1.A + first * s1.step;
+    co[0][h] = i * (uint32_t)s0.step;
+    co[1][h] = i * (uint32_t)s1.step;
   }
-  const uint32_t abytes[2] = {(uint32_t)(RT * kt0 * kFrag), (uint32_t)(RT * (s1.K >> 5) * kFrag)};
+  const uint32_t abytes[2] = {(uint32_t)((RT - 1) * s0.step) + (uint32_t)(kt0 * kFrag),
+                              (uint32_t)((RT - 1) * s1.step) + (uint32_t)((s1.K >> 5) * kFrag)};
   const int cdst = (min(wave / S, RT - 1) * S + ck) * kFrag;
   auto copy_a = [&](uint8_t* st, int s) {
     const int g = min(s * S + ck, ntiles - 1);
@@ -634,8 +636,8 @@ __global__ __launch_bounds__(NT, 2) void gate_f32_kernel(GateArgs g) {
   }
   auto init = [&]() { bias_init<T>(acc, bias, zb, rt.sign0); };
   const uint64_t zpos = (uint64_t)rt.probe * g.zc_stride;
-  const Seg s0{gl.x, gl.w_ih, gl.off_ih, gl.El, T::kZ ? gl.zc_ih + zpos : nullptr};
-  const Seg s1{gl.hprev, gl.w_hh, gl.off_hh, H, T::kZ ? gl.zc_hh + zpos : nullptr};
+  const Seg s0{gl.x, (gl.El >> 5) * kFrag, gl.w_ih, gl.off_ih, gl.El, T::kZ ? gl.zc_ih + zpos : nullptr};
+  const Seg s1{gl.hprev, gl.hstep, gl.w_hh, gl.off_hh, H, T::kZ ? gl.zc_hh + zpos : nullptr};
   mainloop<T, kSplit>(
       acc, s0, s1, 2, rt, 4 * H, __builtin_amdgcn_readfirstlane(wave * H + u0),
       [&](int ct) { return 16 * ct + (lane & 15); }, g.packed, g.key, g.i0 + (uint32_t)rt.probe, g.eps, T::kBits ? g.bits + (uint64_t)rt.probe * g.bits_stride : nullptr, st0, st1, init);
@@ -745,7 +747,7 @@ __global__ __launch_bounds__(NT, 2) void head_f32_kernel(HeadArgs g) {
     zb[ct] = g.zbo[(int64_t)rt.probe * V + row0 + col(ct)];
   }
   auto init = [&]() { bias_init<T>(acc, bias, zb, rt.sign0); };
-  const Seg s0{g.h, g.w_out, g.off_w, g.H,
+  const Seg s0{g.h, (g.H >> 5) * kFrag, g.w_out, g.off_w, g.H,
                T::kZ ? g.zc_out + (uint64_t)rt.probe * g.zc_stride : nullptr};
   mainloop<T, kSplit>(acc, s0, s0, 1, rt, V, row0, col, g.packed, g.key, g.i0 + (uint32_t)rt.probe, g.eps,
                       T::kBits ? g.bits + (uint64_t)rt.probe * g.bits_stride : nullptr, st0, st1, init);

@@ -306,6 +306,8 @@ struct WsPlan {
   size_t x0;         // [M][E] perturbed embeddings of one timestep (bf16 path), [T][M][E] of a chunk (fp32)
   size_t hbuf;       // [L-1][2][M][H]     double-buffered states of the lower layers
   size_t hist;       // [T][M][H]          top-layer states of the current time chunk
+  size_t hzero;      // one row of zeros (packed row tile with fp32 weights): the top layer's state before
+                     // the first timestep where the chunk has one slot (C = 1)
   size_t cbuf;       // f32 [L][M][H]      cell states
   size_t zb;         // f32 [L][N][4H]     eps * z of the gate biases, per probe
   size_t zbo;        // f32 [N][V]         eps * z of the head bias, per probe
@@ -339,6 +341,12 @@ inline int time_chunk(const zo_config& c, int64_t M, int nvt, int32_t C) {
   return C < T ? C : T;
 }
 
+// Bytes of the zero state of a one-slot chunk: one row of fp16, or one packed
+// tile of 16 rows.
+inline size_t zero_state_bytes(const zo_config& c) {
+  return (size_t)c.hidden * act_bytes(c) * (c.wdtype == ZO_WBF16 ? 1 : 16);
+}
+
 inline WsPlan plan_workspace(const zo_config& c, const Rows& r, int32_t C) {
   WsPlan w{};
   const size_t M = (size_t)r.M, E = (size_t)c.embed, H = (size_t)c.hidden, V = (size_t)c.vocab;
@@ -356,6 +364,8 @@ inline WsPlan plan_workspace(const zo_config& c, const Rows& r, int32_t C) {
   w.x0 = take((c.wdtype == ZO_WBF16 ? 1 : (size_t)w.T) * M * E * el);
   w.hbuf = take((L - 1) * 2 * M * H * el);
   w.hist = take((size_t)w.T * M * H * el);
+  w.hzero = p;
+  if (w.T == 1) take(zero_state_bytes(c));
   w.cbuf = take(L * M * H * 4);
   w.zb = take(L * (size_t)r.N * 4 * H * 4);
   w.zbo = take((size_t)r.N * V * 4);

@@ -89,19 +89,24 @@ size_t zo_param_count(const zo_config* cfg) {
   return (size_t)zo::make_layout(*cfg).total;
 }
 
-// Both estimators' passes fit: central (2N passes) and forward (N + 1) differences.
 static zo::WsPlan plan_for(const zo_config* cfg, int32_t N, int32_t B, int32_t C, bool fd) {
   return zo::plan_workspace(*cfg, zo::make_rows(N, B, zo::row_granule(*cfg, N, B, fd), fd), C);
 }
 
+// What the reported sizes hold: both estimators' passes, central (2N passes) and
+// forward (N + 1) differences, with rows that grow with N and B.
+static zo::WsPlan size_plan(const zo_config* cfg, int32_t N, int32_t B, int32_t C, bool fd) {
+  return zo::plan_workspace(*cfg, zo::make_rows(N, B, zo::size_granule(*cfg, fd), fd), C);
+}
+
 size_t zo_workspace_bytes(const zo_config* cfg, int32_t N, int32_t B, int32_t C) {
   if (!zo::config_valid(cfg) || N < 1 || B < 1 || C < 1) return 0;
-  return std::max(plan_for(cfg, N, B, C, false).total, plan_for(cfg, N, B, C, true).total);
+  return std::max(size_plan(cfg, N, B, C, false).total, size_plan(cfg, N, B, C, true).total);
 }
 
 size_t zo_workspace_bytes_min(const zo_config* cfg, int32_t N, int32_t B, int32_t C) {
   if (!zo::config_valid(cfg) || N < 1 || B < 1 || C < 1) return 0;
-  return std::max(plan_for(cfg, N, B, C, false).min_total, plan_for(cfg, N, B, C, true).min_total);
+  return std::max(size_plan(cfg, N, B, C, false).min_total, size_plan(cfg, N, B, C, true).min_total);
 }
 
 int zo_init(const zo_config* cfg, void* theta, uint64_t seed, void* stream) {

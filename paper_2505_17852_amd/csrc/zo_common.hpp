@@ -148,6 +148,15 @@ inline int row_granule(const zo_config& c, int32_t N, int32_t B, bool fd = false
   }
   return best;
 }
+// The multiple that the reported workspace sizes count with. The bf16 granule
+// above turns with N and B, so the rows of a call are not monotone in them
+// (N = 32 and 33 of a batch of 160 take 12,288 and 10,560 rows); a workspace of a
+// reported size also holds every call with fewer probes, sequences or positions.
+// Every granule divides this one, so no call has more rows than it counts.
+inline int size_granule(const zo_config& c, bool fd) {
+  if (c.wdtype != ZO_WBF16) return kRowGranuleF32;
+  return fd ? kTileRows[0] : kTileRows[0] / 2;
+}
 // Bytes of one activation value: fp16 (bf16 weights), three bf16 parts (fp32 weights).
 inline size_t act_bytes(const zo_config& c) { return c.wdtype == ZO_WBF16 ? 2 : 6; }
 
@@ -399,13 +408,15 @@ inline WsPlan plan_workspace(const zo_config& c, const Rows& r, int32_t C) {
 // chunks of kTimeChunk), so that the shapes it takes do not depend on how the
 // forward lays out its buffers; a workspace takes at most 1.5 times it.
 inline size_t noalloc_account(const zo_config& c, int32_t N, int32_t B, int32_t C, bool fd) {
-  if (c.wdtype == ZO_WBF16) return plan_workspace(c, make_rows(N, B, fd ? 256 : 128, fd), C).min_total;
-  const size_t M = (size_t)make_rows(N, B, fd ? 64 : 32, fd).M, T = (size_t)(C < kTimeChunk ? C : kTimeChunk);
+  const bool b16 = c.wdtype == ZO_WBF16;
+  const int g = (b16 ? 128 : 32) * (fd ? 2 : 1);
+  const size_t M = (size_t)make_rows(N, B, g, fd).M, T = (size_t)(C < kTimeChunk ? C : kTimeChunk);
   const size_t E = (size_t)c.embed, H = (size_t)c.hidden, V = (size_t)c.vocab, L = (size_t)c.n_layers;
-  const size_t nvt = (V + kVocabTile - 1) / kVocabTile;
+  const size_t nvt = (V + (size_t)vocab_tile(c) - 1) / (size_t)vocab_tile(c), el = b16 ? 2 : 4;
   size_t p = 0;
-  for (size_t bytes : {T * M * E * 4, (L - 1) * 2 * M * H * 4, T * M * H * 4, L * M * H * 4, L * (size_t)N * 4 * H * 4,
-                       (size_t)N * V * 4, nvt * T * M * 4, nvt * T * M * 4, T * M * 4, M * 8})
+  for (size_t bytes : {(b16 ? 1 : T) * M * E * el, (L - 1) * 2 * M * H * el, T * M * H * el, L * M * H * 4,
+                       L * (size_t)N * 4 * H * 4, (size_t)N * V * 4, nvt * T * M * 4, nvt * T * M * 4, T * M * 4, M * 8,
+                       b16 ? (size_t)make_zcache_map(c).pg * 2 : (size_t)0})
     p = align_up(p + bytes, 256);
   return p;
 }

@@ -3,7 +3,9 @@ order), without a GPU: zo_api.hip and k_forward.hip built for the host with
 their kernel launchers replaced by checks (tests/helpers/forward_plan_driver.cpp).
 Every buffer of every launch lies inside the workspace and apart from the
 others, and no launch writes a state that its other workgroups still read."""
+import math
 import os
+import random
 import subprocess
 
 import pytest
@@ -78,3 +80,49 @@ def test_states_are_not_written_while_read(calls, zo, C, wdtype):
                     lines += [(cfg, fd, N, B, C, ws) for fd in (0, 1)]
                 lines.append((cfg, 2, N, B, C, 0))
     assert all(o[0] == zo.ZO_OK for o in calls(lines))
+
+
+def _draw(rng, wdtype):
+    g = 64 if wdtype == wl.BF16 else 32
+
+    def lg(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    cfg = model(rng.choice([1, 2, 3, 6]), lg(1, 50000), g * lg(1, 20), g * lg(1, 20), wdtype,
+                rng.choice([wl.RADEMACHER, wl.GAUSSIAN]))
+    return cfg, (lg(1, 600), lg(1, 300), lg(1, 60))
+
+
+# (cfg, larger call, smaller call): N, B, C
+REUSE = {
+    wl.BF16: [(model(2, 7401, 832, 1088, wl.BF16, wl.RADEMACHER), (38, 166, 27), (37, 159, 27)),
+              (model(4, 1536, 1024, 64, wl.BF16, wl.GAUSSIAN), (28, 6, 61), (17, 6, 41)),
+              (model(2, 10000, 512, 768, wl.BF16, wl.RADEMACHER), (33, 160, 32), (32, 160, 32)),
+              (model(2, 10000, 512, 768, wl.BF16, wl.GAUSSIAN), (33, 160, 32), (32, 160, 32))],
+}
+
+
+@pytest.mark.parametrize("wdtype", list(REUSE), ids=lambda w: "bf16" if w == wl.BF16 else "fp32")
+def test_a_workspace_holds_every_smaller_call(calls, zo, wdtype):
+    """A workspace sized for a call also holds every call with at most as many
+    probes, sequences and positions, with the caches that the smaller call has
+    in a workspace of its own."""
+    rng = random.Random(5)
+    pairs = list(REUSE[wdtype])
+    for _ in range(1000):
+        cfg, big = _draw(rng, wdtype)
+        small = list(big)
+        for k in range(3):
+            if rng.random() < 0.6:  # a little less, or anything less
+                small[k] = max(1, big[k] - rng.randint(0, 3)) if rng.random() < 0.5 else rng.randint(1, big[k])
+        pairs.append((cfg, big, tuple(small)))
+    lines, own = [], []
+    for cfg, big, small in pairs:
+        for size in (zo.workspace_bytes, zo.workspace_bytes_min):
+            assert size(cfg, *small) <= size(cfg, *big), (cfg, big, small)
+            for fd in (0, 1):
+                lines.append((cfg, fd, *small, size(cfg, *big)))
+                own.append((cfg, fd, *small, size(cfg, *small)))
+    for line, mine, a, b in zip(lines, own, calls(lines), calls(own)):
+        assert a[0] == b[0] == zo.ZO_OK, (line, a, b)
+        assert a[3] & b[3] == b[3], (line, mine, a, b)

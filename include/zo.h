@@ -119,22 +119,29 @@ size_t zo_param_count(const zo_config* cfg);
 
 /* Bytes of device workspace zo_perturbed_losses (or zo_fd_losses) uses for N probes and a
  * batch of B sequences of C positions; 0 if the arguments are invalid.
- * Host only. With bf16 weights every workspace holds an fp16 copy of the
- * weight matrices (every W_ih, W_hh and W_out; P_g values), with fp32 weights
- * a packed fp32 copy and, for sign probes, the probes' sign words (N P / 8
- * bytes), all written by the call. With normal probes this includes the probe cache, written once per
+ * Host only. A workspace of this size also holds every call with at most N
+ * probes, B sequences and C positions, with the caches of that call. With bf16
+ * weights every workspace holds an fp16 copy of the
+ * weight matrices (every W_ih, W_hh and W_out; P_g values). With normal probes
+ * this includes the probe cache, written once per
  * call and read by every timestep instead of regenerating the probe in every
  * tile (the results are bit-identical either way): N * P_g values of eps z
  * for fp32 weights; 2 * N * P_g fp16 values for bf16 weights, each probe's
  * perturbed weights fp16(w + fp16(eps z)) and fp16(w - fp16(eps z)) (fused
  * products), or fp16(eps z) (two-stream products). With
- * sign probes and bf16 weights it includes the sign-probe cache (below); with
- * sign probes and fp32 weights it equals zo_workspace_bytes_min. */
+ * sign probes it includes the probes' sign words (N P / 8 bytes; with bf16
+ * weights the sign-probe cache below), with fp32 weights a packed copy of the
+ * weight matrices where the call is long enough to gain from it; with fp32
+ * weights, words or a copy of more than 8 GiB are used in a workspace that has room for
+ * them but not counted. */
 size_t zo_workspace_bytes(const zo_config* cfg, int32_t N, int32_t B, int32_t C);
 
-/* The smallest workspace zo_perturbed_losses accepts: without the probe
- * cache (normal probes are then regenerated in every tile). A workspace of
- * at least zo_workspace_bytes() enables the cache. Host only. */
+/* A workspace without those caches (probes are then regenerated in every
+ * tile; the results are the same), as small as holds every call with at most N
+ * probes, B sequences and C positions. With fp32 weights up to 16 MiB of caches and
+ * longer time chunks are counted all the same, so for a small model it equals
+ * zo_workspace_bytes, and a call uses the caches that fit whatever the size.
+ * Host only. */
 size_t zo_workspace_bytes_min(const zo_config* cfg, int32_t N, int32_t B, int32_t C);
 
 /* Initialisation: every parameter ~ U(-1/sqrt(H), 1/sqrt(H)), drawn from
@@ -166,8 +173,8 @@ int zo_init(const zo_config* cfg, void* theta, uint64_t seed, void* stream);
  *            next-token cross-entropy in nats at theta + eps z and at
  *            theta - eps z (0 when the mask selects nothing)
  *   workspace, ws_bytes  device scratch of at least zo_workspace_bytes_min()
- *            (normal probes: at least zo_workspace_bytes() to use the probe
- *            cache; same results, fewer probe regenerations)
+ *            (zo_workspace_bytes() to use the caches; same results, fewer
+ *            probe regenerations)
  * Returns ZO_OK, ZO_EINVAL, ZO_ESHAPE, ZO_ENOMEM or ZO_EDEVICE.
  * fp32 weights: each matrix product uses the perturbed weights w +- eps z
  * (one fp32 rounding). bf16 weights: the fused or the two-stream products by

@@ -52,7 +52,7 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 // Workspace of zo_perturbed_losses_noalloc: a fixed device array, one copy per
 // device, held until the process ends, half as large again as the account
-// (noalloc_account) that a call is held against. In host code `scratch` names a host
+// (account_bytes) that a call is held against. In host code `scratch` names a host
 // stand-in; its device address on the current device comes from
 // hipGetSymbolAddress, once per device, and only that address is ever used.
 constexpr size_t kScratchBytes = (size_t)ZO_NOALLOC_WORKSPACE_BYTES / 2 * 3 + (1u << 16);
@@ -89,24 +89,17 @@ size_t zo_param_count(const zo_config* cfg) {
   return (size_t)zo::make_layout(*cfg).total;
 }
 
-static zo::WsPlan plan_for(const zo_config* cfg, int32_t N, int32_t B, int32_t C, bool fd) {
-  return zo::plan_workspace(*cfg, zo::make_rows(N, B, zo::row_granule(*cfg, N, B, fd), fd), C);
+// Both estimators' passes fit: central (2N passes) and forward (N + 1) differences.
+static zo::WsSizes sizes_of(const zo_config* cfg, int32_t N, int32_t B, int32_t C) {
+  if (!zo::config_valid(cfg) || N < 1 || B < 1 || C < 1) return zo::WsSizes{0, 0};
+  const zo::WsSizes a = zo::workspace_sizes(*cfg, N, B, C, false), b = zo::workspace_sizes(*cfg, N, B, C, true);
+  return zo::WsSizes{std::max(a.full, b.full), std::max(a.smallest, b.smallest)};
 }
 
-// What the reported sizes hold: both estimators' passes, central (2N passes) and
-// forward (N + 1) differences, with rows that grow with N and B.
-static zo::WsPlan size_plan(const zo_config* cfg, int32_t N, int32_t B, int32_t C, bool fd) {
-  return zo::plan_workspace(*cfg, zo::make_rows(N, B, zo::size_granule(*cfg, fd), fd), C);
-}
-
-size_t zo_workspace_bytes(const zo_config* cfg, int32_t N, int32_t B, int32_t C) {
-  if (!zo::config_valid(cfg) || N < 1 || B < 1 || C < 1) return 0;
-  return std::max(size_plan(cfg, N, B, C, false).total, size_plan(cfg, N, B, C, true).total);
-}
+size_t zo_workspace_bytes(const zo_config* cfg, int32_t N, int32_t B, int32_t C) { return sizes_of(cfg, N, B, C).full; }
 
 size_t zo_workspace_bytes_min(const zo_config* cfg, int32_t N, int32_t B, int32_t C) {
-  if (!zo::config_valid(cfg) || N < 1 || B < 1 || C < 1) return 0;
-  return std::max(size_plan(cfg, N, B, C, false).min_total, size_plan(cfg, N, B, C, true).min_total);
+  return sizes_of(cfg, N, B, C).smallest;
 }
 
 int zo_init(const zo_config* cfg, void* theta, uint64_t seed, void* stream) {
@@ -123,7 +116,7 @@ int zo_init(const zo_config* cfg, void* theta, uint64_t seed, void* stream) {
 static int forward_call(const zo_config* cfg, const void* theta, uint64_t seed, float eps, int32_t N,
                         uint32_t i0, const int32_t* tokens, const uint8_t* mask, int32_t B, int32_t C,
                         float* L1, float* L2, void* workspace, size_t ws_bytes, int32_t products,
-                        void* stream, bool fd, const char* name, bool regen = false) {
+                        void* stream, bool fd, const char* name) {
   zo::PhaseRange range(name);
   int st = check_config(cfg);
   if (st) return st;
@@ -148,11 +141,9 @@ static int forward_call(const zo_config* cfg, const void* theta, uint64_t seed, 
     return fail(ZO_EINVAL, "probe indices i0 .. i0+N-1 must fit in 32 bits");
   const zo::Rows rows = zo::make_rows(N, B, zo::row_granule(*cfg, N, B, fd), fd);
   if (rows.M > (int64_t)1 << 30) return fail(ZO_ESHAPE, "rows of all passes too many");
-  const zo::WsPlan plan = zo::plan_workspace(*cfg, rows, C);
-  // regen: the fixed scratch may lack room for the fp32 path's packed weights
-  // and sign words (the kernels then read theta itself and regenerate them)
-  const size_t need = regen ? plan.regen_total : plan.min_total;
-  if (ws_bytes < need) return fail(ZO_ENOMEM, "workspace of %zu bytes < %zu required", ws_bytes, need);
+  zo::Caches caches;
+  const zo::WsPlan plan = zo::plan_for_bytes(*cfg, rows, C, ws_bytes, &caches);
+  if (ws_bytes < plan.total) return fail(ZO_ENOMEM, "workspace of %zu bytes < %zu required", ws_bytes, plan.total);
   zo::ForwardArgs a;
   a.cfg = *cfg;
   a.lay = zo::make_layout(*cfg);
@@ -174,18 +165,11 @@ static int forward_call(const zo_config* cfg, const void* theta, uint64_t seed, 
     a.split = cfg->wdtype == ZO_WBF16 && eps < ZO_BF16_FUSED_EPS_MIN;
   else
     a.split = products == ZO_PRODUCTS_SPLIT;
-  // the probe cache is used when the workspace has room for it
-  a.zc = (zo::probe_cache_kind(*cfg) && ws_bytes >= plan.total) ? (char*)workspace + plan.zcache : nullptr;
-  // the packed weight copy: one launch more, made up for after a few hundred k
-  // tiles per column (c1, 96 of them: 232 us per step without it, 238 with;
-  // c2's evaluation, 3,600: 2.75 against 2.62 ms)
-  const bool pack = (int64_t)C * (cfg->embed + cfg->hidden) / 32 >= 256 && ws_bytes >= plan.min_total;
-  a.wpack = cfg->wdtype == ZO_WFP32 && pack ? (const float*)((char*)workspace + plan.wpack) : nullptr;
-  // the sign words: always with fp32 weights (min_total holds them), with bf16
-  // weights when the workspace has room for them (total does)
-  a.bits = cfg->probe == ZO_RADEMACHER && ws_bytes >= (cfg->wdtype == ZO_WFP32 ? plan.min_total : plan.total)
-               ? (uint32_t*)((char*)workspace + plan.bits)
-               : nullptr;
+  // without them the kernels regenerate the probes and read the weights in place
+  const bool sign = cfg->probe == ZO_RADEMACHER;
+  a.zc = caches.probes && !sign ? (char*)workspace + plan.zcache : nullptr;
+  a.bits = caches.probes && sign ? (uint32_t*)((char*)workspace + plan.bits) : nullptr;
+  a.wpack = caches.wpack ? (const float*)((char*)workspace + plan.wpack) : nullptr;
   a.zmap = zo::make_zcache_map(*cfg);
   a.w16 = cfg->wdtype == ZO_WBF16 ? (char*)workspace + plan.w16 : nullptr;
   return device_status(zo::launch_forward(a, (hipStream_t)stream), name);
@@ -214,19 +198,19 @@ int zo_perturbed_losses_noalloc(const zo_config* cfg, const void* theta, uint64_
   if (N < 1 || B < 1 || C < 1) return fail(ZO_EINVAL, "N, B and C must be >= 1");
   // the sizes are checked before the scratch array is first touched
   if (!zo::config_valid(cfg)) return fail(ZO_EINVAL, "invalid workspace request");
-  const size_t need = std::max(zo::noalloc_account(*cfg, N, B, C, false), zo::noalloc_account(*cfg, N, B, C, true));
+  const size_t need = std::max(zo::account_bytes(*cfg, N, B, C, false), zo::account_bytes(*cfg, N, B, C, true));
   if (need > (size_t)ZO_NOALLOC_WORKSPACE_BYTES)
     return fail(ZO_ENOMEM, "zo_perturbed_losses_noalloc: %zu bytes of workspace needed, the fixed scratch holds %zu",
                 need, (size_t)ZO_NOALLOC_WORKSPACE_BYTES);
   void* ws = nullptr;
   st = scratch_address(&ws);
   if (st) return st;
-  // the whole array: the probe cache and the sign words are used when they
-  // fit in it (the results are the same either way)
+  // the whole array: the caches are used when they fit in it (the results are
+  // the same either way)
   const size_t bytes = kScratchBytes;
   zo::g_profile_suppressed = true;
   st = forward_call(cfg, theta, seed, eps, N, i0, tokens, mask, B, C, Lplus, Lminus, ws, bytes, ZO_PRODUCTS_AUTO,
-                    stream, false, "zo_perturbed_losses_noalloc", true);
+                    stream, false, "zo_perturbed_losses_noalloc");
   zo::g_profile_suppressed = false;
   return st;
 }
@@ -266,7 +250,8 @@ int zo_update(const zo_config* cfg, void* theta, uint64_t seed, float eps, float
 
 size_t zo_probe_bits_offset(const zo_config* cfg, int32_t N, int32_t B, int32_t C) {
   if (!zo::config_valid(cfg) || N < 1 || B < 1 || C < 1 || !zo::bit_cache_kind(*cfg)) return 0;
-  return plan_for(cfg, N, B, C, false).bits;
+  const zo::Rows rows = zo::make_rows(N, B, zo::row_granule(*cfg, N, B), false);
+  return zo::plan_workspace(*cfg, rows, zo::least_time_chunk(*cfg, C), zo::Caches{true, false}).bits;
 }
 
 int zo_update_cached(const zo_config* cfg, void* theta, uint64_t seed, float eps, float lr, int32_t N,

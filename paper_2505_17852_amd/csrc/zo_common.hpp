@@ -3,10 +3,10 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stddef.h>
-
-#include <initializer_list>
-
 #include <stdint.h>
+
+#include <algorithm>
+#include <initializer_list>
 
 #include "../../include/zo.h"
 
@@ -225,8 +225,8 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // fp16(eps z) (bf16 weights), for probes i0 .. i0+N-1. Layout: probe n's
 // block of P_g values (the matrices in theta order) at n * P_g; each matrix
 // packed like the weight copy the kernels read: row_piece (fp32 weights) or
-// fragment-packed fp16 (bf16 weights), both in zo_pack.hpp. Sign probes are cheap to
-// regenerate and are never cached. The same map places the matrices of the
+// fragment-packed fp16 (bf16 weights), both in zo_pack.hpp. Sign
+// probes are cached as bits instead (below). The same map places the matrices of the
 // bf16 path's fp16 weight copy; there the head matrix is padded with zero
 // rows to a whole number of 256-wide vocabulary tiles.
 struct ZCacheMap {
@@ -254,21 +254,17 @@ inline ZCacheMap make_zcache_map(const zo_config& c) {
   return m;
 }
 
-inline bool probe_cache_kind(const zo_config& c) { return c.probe == ZO_GAUSSIAN; }
-
-// Bit-packed sign-probe cache (bf16 weights with sign probes): the sign words
-// of probes i0 .. i0+N-1 over the whole parameter vector, written once per call
-// (one Philox block per 128 parameters and probe) and read by the forward
-// kernels in place of regenerating them in every K tile: probe n's word w, the
+// Bit-packed sign-probe cache (sign probes): the sign words of probes i0 ..
+// i0+N-1 over the whole parameter vector, written once per call (one Philox
+// block per 128 parameters and probe) and read by the forward kernels in place of regenerating them in every K tile: probe n's word w, the
 // signs of parameters 32 w .. 32 w + 31 (a set bit for z = +1), at
 // n * bit_words(P) + w, unshuffled: parameter 32 w + 2 i at bit i and
 // 32 w + 2 i + 1 at bit 16 + i (sign_word_unshuffle of the generator's word),
 // the order in which the bf16 products turn a pair of flags into a packed
 // fp16 pair with one shift. The update can read the same words
 // (zo_update_cached) instead of regenerating them.
-// With fp32 weights every workspace holds the same words (fp32's share of a
-// probe is 32 times its bits), for the forward's own use; only the bf16 ones
-// are offered to callers.
+// With fp32 weights the words are for the forward's own use; only the bf16
+// ones are offered to callers (bit_cache_kind).
 inline bool bit_cache_kind(const zo_config& c) { return c.probe == ZO_RADEMACHER && c.wdtype == ZO_WBF16; }
 __host__ __device__ inline uint64_t bit_words(uint64_t P) { return (P + 127) / 128 * 4; }
 
@@ -325,29 +321,43 @@ struct WsPlan {
   size_t ptgt;       // f32 [T*M]          target logit
   size_t row_loss;   // f64 [M]            masked loss sum of each row
   size_t w16;        // f16 [P_g]          bf16 weights: the product matrices in fp16 (ZCacheMap layout)
-  size_t regen_total;  // bytes with which the forward can run at all (every probe regenerated in every tile)
+  // what the plan's Caches ask for; everything else is needed
   size_t wpack;      // f32 [P_g]          fp32 weights: the product matrices packed (row_piece)
-  size_t min_total;  // bytes the entry points ask for at least: as above, and the fp32 path's packed
-                     // weights and sign words
   size_t zcache;     // probe cache (normal probes; see ZCacheMap): fp32 weights [N][P_g] eps z;
                      // bf16 weights [N][2][P_g] fp16: probe n's perturbed weights
                      // fp16(w + fp16(eps z)) and fp16(w - fp16(eps z)) (fused products), or
                      // fp16(eps z) in the first N P_g values (two-stream products)
   size_t bits;       // sign words [N][bit_words(P)] u32 (sign probes)
-  size_t total;      // bytes with the probe cache
+  size_t total;      // bytes of the plan
   int nvt;           // vocabulary tiles
   int T;             // time chunk
 };
 
+// The parts of a plan that save work where there is room for them.
+struct Caches {
+  bool probes;  // normal probes: zcache; sign probes: bits
+  bool wpack;   // fp32 weights: the packed copy
+};
+
 // Time steps per chunk. bf16 path: kTimeChunk. fp32 path: as many (8 to 64) as
 // keep the chunk's buffers below 16 MiB: small models then take few head
-// launches, and the states of large ones stay near the caches.
+// launches, and the states of large ones stay near the caches. A workspace
+// without room for that takes fewer (plan_for_bytes), down to
+// least_time_chunk: two, which keeps the state being written apart from the
+// one before it.
+constexpr size_t kChunkBytes = (size_t)16 << 20;
+inline size_t chunk_step_bytes(const zo_config& c, int64_t M, int nvt) {
+  return (size_t)M * (((size_t)c.embed + (size_t)c.hidden) * act_bytes(c) + 8 * (size_t)nvt + 4);
+}
 inline int time_chunk(const zo_config& c, int64_t M, int nvt, int32_t C) {
   if (c.wdtype == ZO_WBF16) return C < kTimeChunk ? C : kTimeChunk;
-  const double step = (double)M * (((double)c.embed + c.hidden) * (double)act_bytes(c) + 8.0 * nvt + 4.0);
-  const double n = 16.0 * 1024 * 1024 / step;
+  const size_t n = kChunkBytes / chunk_step_bytes(c, M, nvt);
   const int T = n < 8 ? 8 : n > 64 ? 64 : (int)n;
   return C < T ? C : T;
+}
+inline int least_time_chunk(const zo_config& c, int32_t C) {
+  const int least = c.wdtype == ZO_WBF16 ? kTimeChunk : 2;
+  return C < least ? C : least;
 }
 
 // Bytes of the zero state of a one-slot chunk: one row of fp16, or one packed
@@ -356,14 +366,26 @@ inline size_t zero_state_bytes(const zo_config& c) {
   return (size_t)c.hidden * act_bytes(c) * (c.wdtype == ZO_WBF16 ? 1 : 16);
 }
 
-inline WsPlan plan_workspace(const zo_config& c, const Rows& r, int32_t C) {
+inline int vocab_tiles(const zo_config& c) { return (c.vocab + vocab_tile(c) - 1) / vocab_tile(c); }
+inline size_t probe_cache_bytes(const zo_config& c, int32_t N) {
+  if (c.probe == ZO_RADEMACHER) return (size_t)N * bit_words(make_layout(c).total) * 4;
+  return (size_t)N * make_zcache_map(c).pg * (c.wdtype == ZO_WBF16 ? 2 * 2 : 4);
+}
+inline size_t wpack_bytes(const zo_config& c) { return (size_t)make_zcache_map(c).pg * 4; }
+// The packed weight copy costs one launch more, made up for after a few hundred
+// k tiles per column (c1, 96 of them: 232 us per step without it, 238 with;
+// c2's evaluation, 3,600: 2.75 against 2.62 ms).
+inline bool wpack_pays(const zo_config& c, int32_t C) {
+  return c.wdtype == ZO_WFP32 && (int64_t)C * ((int64_t)c.embed + c.hidden) / 32 >= 256;
+}
+
+inline WsPlan plan_workspace(const zo_config& c, const Rows& r, int T, Caches caches) {
   WsPlan w{};
   const size_t M = (size_t)r.M, E = (size_t)c.embed, H = (size_t)c.hidden, V = (size_t)c.vocab;
   const size_t L = (size_t)c.n_layers;
   const size_t el = act_bytes(c);
-  const size_t vt = (size_t)vocab_tile(c);
-  w.nvt = (int)((V + vt - 1) / vt);
-  w.T = time_chunk(c, r.M, w.nvt, C);
+  w.nvt = vocab_tiles(c);
+  w.T = T;
   size_t p = 0;
   auto take = [&](size_t bytes) {
     size_t o = p;
@@ -384,30 +406,51 @@ inline WsPlan plan_workspace(const zo_config& c, const Rows& r, int32_t C) {
   w.row_loss = take(M * 8);
   w.w16 = p;
   if (c.wdtype == ZO_WBF16) take((size_t)make_zcache_map(c).pg * 2);
-  w.regen_total = p;
   w.wpack = p;
-  if (c.wdtype == ZO_WFP32) take((size_t)make_zcache_map(c).pg * 4);
-  const bool sign = c.probe == ZO_RADEMACHER;
-  const size_t bits = sign ? (size_t)r.N * bit_words(make_layout(c).total) * 4 : 0;
-  w.bits = p;
-  if (sign && c.wdtype == ZO_WFP32) take(bits);
-  w.min_total = p;
-  w.zcache = p;
-  if (probe_cache_kind(c)) take((size_t)r.N * make_zcache_map(c).pg * (c.wdtype == ZO_WBF16 ? 2 * 2 : 4));
-  if (bit_cache_kind(c)) {
-    w.bits = p;
-    take(bits);
-  }
+  if (caches.wpack) take(wpack_bytes(c));
+  w.zcache = w.bits = p;
+  if (caches.probes) take(probe_cache_bytes(c, r.N));
   w.total = p;
   return w;
 }
 
-// What zo_perturbed_losses_noalloc holds against its fixed size: a fixed
-// account of a call's needs (batches padded to 128 or 256 sequences with bf16
-// weights, to 32 or 64 with fp32 ones, there also 4 bytes per activation and
-// chunks of kTimeChunk), so that the shapes it takes do not depend on how the
-// forward lays out its buffers; a workspace takes at most 1.5 times it.
-inline size_t noalloc_account(const zo_config& c, int32_t N, int32_t B, int32_t C, bool fd) {
+// The plan of a call in a workspace of ws_bytes: the caches that fit beside a
+// chunk of at least 8 timesteps (the probes' first: a regenerated probe costs
+// more than a weight read in place), then the longest chunk up to the preferred
+// one. total > ws_bytes: the workspace holds no plan, and total is what the
+// smallest takes.
+inline WsPlan plan_for_bytes(const zo_config& c, const Rows& r, int32_t C, size_t ws_bytes, Caches* used) {
+  const int most = time_chunk(c, r.M, vocab_tiles(c), C), least = least_time_chunk(c, C);
+  const int mid = most < 8 || c.wdtype == ZO_WBF16 ? most : 8;
+  WsPlan w{};
+  auto fits = [&](int T, Caches k) {
+    w = plan_workspace(c, r, T, k);
+    *used = k;
+    return w.total <= ws_bytes;
+  };
+  const bool pack = wpack_pays(c, C);
+  for (Caches k : {Caches{true, true}, Caches{true, false}, Caches{false, true}, Caches{false, false}}) {
+    if (k.wpack && !pack) continue;
+    if (!fits(mid, k)) continue;
+    for (int T = most; T > mid; --T)
+      if (fits(T, k)) return w;
+    fits(mid, k);
+    return w;
+  }
+  for (int T = mid; T > least; --T)
+    if (fits(T, Caches{false, false})) return w;
+  fits(least, Caches{false, false});
+  return w;
+}
+
+// Bytes that a call with N probes and B x C positions took before the fp32
+// states were stored in three parts: batches padded to 128 or 256 sequences with
+// bf16 weights, to 32 or 64 with fp32 ones, there also 4 bytes per activation,
+// chunks of kTimeChunk timesteps. It grows with N, B and C and does not
+// follow how the forward lays out its buffers; zo_perturbed_losses_noalloc holds
+// it against its fixed size, and the smallest fp32 workspace is at least as
+// large.
+inline size_t account_bytes(const zo_config& c, int32_t N, int32_t B, int32_t C, bool fd) {
   const bool b16 = c.wdtype == ZO_WBF16;
   const int g = (b16 ? 128 : 32) * (fd ? 2 : 1);
   const size_t M = (size_t)make_rows(N, B, g, fd).M, T = (size_t)(C < kTimeChunk ? C : kTimeChunk);
@@ -419,6 +462,41 @@ inline size_t noalloc_account(const zo_config& c, int32_t N, int32_t B, int32_t 
                        b16 ? (size_t)make_zcache_map(c).pg * 2 : (size_t)0})
     p = align_up(p + bytes, 256);
   return p;
+}
+
+// Reported workspace sizes. A workspace of the size of (N, B, C) holds every call
+// with at most as many probes, sequences and positions, so each part grows with
+// them: rows by size_granule, and for the fp32 chunk, whose length falls with
+// the rows, the bound min(min(C, 64) steps, max(16 MiB, min(C, 8) steps)) of
+// time_chunk's bytes.
+//   full      every cache, except sign words or packed weights (fp32) beyond
+//             kExtraCap each: those had no share in the size when they were
+//             not stored, and a call that was close to the device's memory
+//             stays below it
+//   smallest  no caches beyond 16 MiB of them and of longer chunks (a small
+//             model's smallest workspace then has what its full one has), and
+//             at least account_bytes
+constexpr size_t kExtraCap = (size_t)8 << 30;
+struct WsSizes {
+  size_t full, smallest;
+};
+inline WsSizes workspace_sizes(const zo_config& c, int32_t N, int32_t B, int32_t C, bool fd) {
+  const Rows r = make_rows(N, B, size_granule(c, fd), fd);
+  const int least = least_time_chunk(c, C);
+  if (c.wdtype == ZO_WBF16)
+    return WsSizes{plan_workspace(c, r, least, Caches{true, false}).total,
+                   plan_workspace(c, r, least, Caches{false, false}).total};
+  // a plan without its chunk's buffers and with room for the zero state and each buffer's alignment
+  const size_t step = chunk_step_bytes(c, r.M, vocab_tiles(c));
+  const size_t fixed = plan_workspace(c, r, 0, Caches{false, false}).total + zero_state_bytes(c) + 8 * 256;
+  const size_t need = fixed + (size_t)least * step;
+  size_t want = fixed + std::min((size_t)std::min(C, 64) * step, std::max(kChunkBytes, (size_t)std::min(C, 8) * step));
+  if (wpack_pays(c, C) && wpack_bytes(c) <= kExtraCap) want += align_up(wpack_bytes(c), 256);
+  size_t zc = 0;
+  if (c.probe == ZO_RADEMACHER) want += align_up(std::min(probe_cache_bytes(c, N), kExtraCap), 256);
+  else zc = align_up(probe_cache_bytes(c, N), 256);
+  const size_t smallest = std::max(account_bytes(c, N, B, C, fd), std::min(want, need + kChunkBytes));
+  return WsSizes{std::max(smallest, want) + zc, smallest};
 }
 
 }  // namespace zo

@@ -99,6 +99,8 @@ REUSE = {
               (model(4, 1536, 1024, 64, wl.BF16, wl.GAUSSIAN), (28, 6, 61), (17, 6, 41)),
               (model(2, 10000, 512, 768, wl.BF16, wl.RADEMACHER), (33, 160, 32), (32, 160, 32)),
               (model(2, 10000, 512, 768, wl.BF16, wl.GAUSSIAN), (33, 160, 32), (32, 160, 32))],
+    wl.FP32: [(model(2, 256, 128, 256, wl.FP32, wl.RADEMACHER), (1, 81, 256), (1, 80, 256)),
+              (model(1, 128, 32, 32, wl.FP32, wl.GAUSSIAN), (1, 32, 64), (1, 32, 9))],
 }
 
 
@@ -125,4 +127,43 @@ def test_a_workspace_holds_every_smaller_call(calls, zo, wdtype):
                 own.append((cfg, fd, *small, size(cfg, *small)))
     for line, mine, a, b in zip(lines, own, calls(lines), calls(own)):
         assert a[0] == b[0] == zo.ZO_OK, (line, a, b)
-        assert a[3] & b[3] == b[3], (line, mine, a, b)
+        assert a[3] & b[3] & 3 == b[3] & 3, (line, mine, a, b)
+
+
+def _plain_f32(cfg, N, B, C):
+    """Bytes of a call with fp32 activations, batches padded to 32 (64 for forward
+    differences) and chunks of 16 timesteps: the smallest fp32 workspace before
+    the states were stored in three parts."""
+    L, V, E, H = cfg["n_layers"], cfg["vocab"], cfg["embed"], cfg["hidden"]
+    T, nvt, size = min(C, 16), (V + 127) // 128, 0
+    for M in (2 * N * ((B + 31) // 32 * 32), (N + 1) * ((B + 63) // 64 * 64)):
+        parts = [T * M * E * 4, (L - 1) * 2 * M * H * 4, T * M * H * 4, L * M * H * 4, L * N * 4 * H * 4, N * V * 4,
+                 nvt * T * M * 4, nvt * T * M * 4, T * M * 4, M * 8]
+        size = max(size, sum((p + 255) // 256 * 256 for p in parts))
+    return size
+
+
+def test_smallest_f32_workspace_needs_no_caches(calls, zo):
+    """The smallest fp32 workspace leaves out the packed weights and the sign
+    words (the forward runs without): calls of at least a chunk of positions run
+    in as many bytes as before either was stored, and the size reported is at
+    most 16 MiB above that."""
+    assert _plain_f32(wl.model_cfg("c2"), 32, 64, 256) == 119078912  # 113.6 MiB
+    cases = [(model(2, 50000, 512, 1024, wl.FP32, wl.RADEMACHER), 96, 32, 16),
+             (model(6, 50000, 1024, 2048, wl.FP32, wl.RADEMACHER), 64, 16, 64)]
+    rng = random.Random(8)
+    while len(cases) < 400:
+        cfg, (N, B, C) = _draw(rng, wl.FP32)
+        cases.append((cfg, N, B, C + 15))
+    for cfg, N, B, C in cases:
+        size, plain = zo.workspace_bytes_min(cfg, N, B, C), _plain_f32(cfg, N, B, C)
+        assert plain <= size <= plain + (16 << 20), (cfg, N, B, C, size, plain)
+    lines = [(cfg, fd, N, B, C, _plain_f32(cfg, N, B, C)) for cfg, N, B, C in cases for fd in (0, 1)]
+    out = calls(lines)
+    assert all(o[0] == zo.ZO_OK for o in out)
+    # and a full one holds both caches
+    full = calls([(cfg, fd, N, B, C, zo.workspace_bytes(cfg, N, B, C)) for cfg, N, B, C in cases for fd in (0, 1)])
+    for line, o in zip(lines, full):
+        cfg, C = line[0], line[4]
+        packs = C * (cfg["embed"] + cfg["hidden"]) // 32 >= 256
+        assert o[0] == zo.ZO_OK and o[3] == (1 if cfg["probe"] == wl.RADEMACHER else 2) + 4 * packs, (line, o)

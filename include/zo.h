@@ -203,9 +203,8 @@ int zo_perturbed_losses_ex(const zo_config* cfg, const void* theta, uint64_t see
  * ZO_NOALLOC_WORKSPACE_BYTES returns ZO_ENOMEM before anything is enqueued;
  * they are counted by a fixed account (bf16 weights: batches padded to a
  * multiple of 128, 256 for what forward differences would need; fp32 weights:
- * 32 or 64, 4 bytes per activation, states of up to 16 timesteps), which
- * zo_workspace_bytes_min() may be above or below; the array is half as large
- * again. Every call on a device shares that device's array:
+ * 32 or 64, 4 bytes per activation, states of up to 16 timesteps); the array is
+ * half as large again, which holds every call within the account. Every call on a device shares that device's array:
  * calls that overlap on one device (concurrent streams or threads) race and
  * must be serialised by the caller. Each call clears what it reads before
  * writing it, so no state carries from one call to the next. Other arguments,

@@ -52,7 +52,11 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 // Workspace of zo_perturbed_losses_noalloc: a fixed device array, one copy per
 // device, held until the process ends, half as large again as the account
-// (account_bytes) that a call is held against. In host code `scratch` names a host
+// (account_bytes) that a call is held against: every buffer of a call's
+// smallest plan (least_time_chunk timesteps, no caches) takes at most 1.5 times
+// its share of the account (an fp32 state 6 bytes for 4, no more rows or
+// timesteps), and the cell states, counted 1.5 times and needed once, leave
+// room for the zero state. In host code `scratch` names a host
 // stand-in; its device address on the current device comes from
 // hipGetSymbolAddress, once per device, and only that address is ever used.
 constexpr size_t kScratchBytes = (size_t)ZO_NOALLOC_WORKSPACE_BYTES / 2 * 3 + (1u << 16);

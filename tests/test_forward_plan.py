@@ -130,15 +130,19 @@ def test_a_workspace_holds_every_smaller_call(calls, zo, wdtype):
         assert a[3] & b[3] & 3 == b[3] & 3, (line, mine, a, b)
 
 
-def _plain_f32(cfg, N, B, C):
-    """Bytes of a call with fp32 activations, batches padded to 32 (64 for forward
-    differences) and chunks of 16 timesteps: the smallest fp32 workspace before
-    the states were stored in three parts."""
+def _plain(cfg, N, B, C):
+    """Bytes of a call with fp32 activations (fp16 with bf16 weights), batches
+    padded to 32 or 128 (twice that for forward differences) and chunks of 16
+    timesteps: the smallest workspace before the fp32 states were stored in three
+    parts and the bf16 tiles got smaller, and the no-alloc entry point's account."""
     L, V, E, H = cfg["n_layers"], cfg["vocab"], cfg["embed"], cfg["hidden"]
-    T, nvt, size = min(C, 16), (V + 127) // 128, 0
-    for M in (2 * N * ((B + 31) // 32 * 32), (N + 1) * ((B + 63) // 64 * 64)):
-        parts = [T * M * E * 4, (L - 1) * 2 * M * H * 4, T * M * H * 4, L * M * H * 4, L * N * 4 * H * 4, N * V * 4,
-                 nvt * T * M * 4, nvt * T * M * 4, T * M * 4, M * 8]
+    b16 = cfg["wdtype"] == wl.BF16
+    g, vt, el = (128, 256, 2) if b16 else (32, 128, 4)
+    T, nvt, size = min(C, 16), (V + vt - 1) // vt, 0
+    pg = sum(4 * H * ((E if l == 0 else H) + H) for l in range(L)) + nvt * vt * H
+    for M in (2 * N * ((B + g - 1) // g * g), (N + 1) * ((B + 2 * g - 1) // (2 * g) * (2 * g))):
+        parts = [(1 if b16 else T) * M * E * el, (L - 1) * 2 * M * H * el, T * M * H * el, L * M * H * 4,
+                 L * N * 4 * H * 4, N * V * 4, nvt * T * M * 4, nvt * T * M * 4, T * M * 4, M * 8, pg * 2 if b16 else 0]
         size = max(size, sum((p + 255) // 256 * 256 for p in parts))
     return size
 
@@ -148,7 +152,7 @@ def test_smallest_f32_workspace_needs_no_caches(calls, zo):
     words (the forward runs without): calls of at least a chunk of positions run
     in as many bytes as before either was stored, and the size reported is at
     most 16 MiB above that."""
-    assert _plain_f32(wl.model_cfg("c2"), 32, 64, 256) == 119078912  # 113.6 MiB
+    assert _plain(wl.model_cfg("c2"), 32, 64, 256) == 119078912  # 113.6 MiB
     cases = [(model(2, 50000, 512, 1024, wl.FP32, wl.RADEMACHER), 96, 32, 16),
              (model(6, 50000, 1024, 2048, wl.FP32, wl.RADEMACHER), 64, 16, 64)]
     rng = random.Random(8)
@@ -156,9 +160,9 @@ def test_smallest_f32_workspace_needs_no_caches(calls, zo):
         cfg, (N, B, C) = _draw(rng, wl.FP32)
         cases.append((cfg, N, B, C + 15))
     for cfg, N, B, C in cases:
-        size, plain = zo.workspace_bytes_min(cfg, N, B, C), _plain_f32(cfg, N, B, C)
+        size, plain = zo.workspace_bytes_min(cfg, N, B, C), _plain(cfg, N, B, C)
         assert plain <= size <= plain + (16 << 20), (cfg, N, B, C, size, plain)
-    lines = [(cfg, fd, N, B, C, _plain_f32(cfg, N, B, C)) for cfg, N, B, C in cases for fd in (0, 1)]
+    lines = [(cfg, fd, N, B, C, _plain(cfg, N, B, C)) for cfg, N, B, C in cases for fd in (0, 1)]
     out = calls(lines)
     assert all(o[0] == zo.ZO_OK for o in out)
     # and a full one holds both caches
@@ -167,3 +171,29 @@ def test_smallest_f32_workspace_needs_no_caches(calls, zo):
         cfg, C = line[0], line[4]
         packs = C * (cfg["embed"] + cfg["hidden"]) // 32 >= 256
         assert o[0] == zo.ZO_OK and o[3] == (1 if cfg["probe"] == wl.RADEMACHER else 2) + 4 * packs, (line, o)
+
+
+@pytest.mark.parametrize("wdtype", [wl.FP32, wl.BF16], ids=["fp32", "bf16"])
+def test_noalloc_array_holds_every_call_its_account_admits(calls, zo, wdtype):
+    """zo_perturbed_losses_noalloc takes a call exactly when its account is at most
+    ZO_NOALLOC_WORKSPACE_BYTES, and then finds room in the array: at the largest
+    number of probes the account admits, and refused at one more."""
+    rng = random.Random(11)
+    shapes = [(model(1, 3, 32, 4096, wl.FP32, wl.RADEMACHER), 32, 1), (model(64, 3, 32, 512, wl.FP32, wl.GAUSSIAN), 32, 9),
+              (model(1, 100, 32, 32, wl.FP32, wl.RADEMACHER), 32, 64)] if wdtype == wl.FP32 else []
+    while len(shapes) < 400:
+        cfg, (_, B, C) = _draw(rng, wdtype)
+        cfg["n_layers"] = rng.choice([1, 2, 3, 6, 20, 64])
+        shapes.append((cfg, B, rng.choice([1, 2, 3, C])))
+    lines, want = [], []
+    for cfg, B, C in shapes:
+        lo, hi = 0, 1 << 20  # account(lo) fits, account(hi) does not
+        while hi - lo > 1:
+            n = (lo + hi) // 2
+            lo, hi = (n, hi) if _plain(cfg, n, B, C) <= zo.NOALLOC_WORKSPACE_BYTES else (lo, n)
+        for n in (lo, hi) if lo else (hi,):
+            lines.append((cfg, 2, n, B, C, 0))
+            want.append(zo.ZO_OK if n == lo else zo.ZO_ENOMEM)
+    assert want.count(zo.ZO_OK) > 250
+    for line, st, o in zip(lines, want, calls(lines)):
+        assert o[0] == st, (line, o)

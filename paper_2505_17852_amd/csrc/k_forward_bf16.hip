@@ -821,7 +821,9 @@ __global__ __launch_bounds__(T::NT, 1) void head_bf16_kernel(HeadArgsB g) {
   const int wm = wave % G::WAVES_M, wn = wave / G::WAVES_M;
   const int lr = lane & 31, lg = lane >> 5;
   int mb, vt;
-  tile_of(blockIdx.x, (int)(g.rows / TM), g.nvt, mb, vt);
+  const int id = (int)block_id(), nm = (int)(g.rows / TM);
+  if (id >= nm * g.nvt) return;
+  tile_of(id, nm, g.nvt, mb, vt);
   if constexpr (kind == kGaussPerturbed || kind == kGaussCached) {
     // Normal-probe caches: the weight operand differs per pass (or probe),
     // so the row blocks tile_of groups on one XCD are taken as one pass
@@ -1133,12 +1135,17 @@ hipError_t launch_gate_bf16(const ForwardArgs& a, int l, const void* x, const vo
   g.bits_stride = bit_words(a.lay.total);
   const TilePlan plan = plan_tiles(a, R.M, 4 * (int64_t)g.H, true);
   int64_t rows = 0;  // rows of the launch
+  bool fits = true;
   auto go = [&](auto kind_tag, auto tm_tag, auto split_tag) {
     constexpr int kind = decltype(kind_tag)::value, tm = decltype(tm_tag)::value;
     using T = Tiles<kind, tm, tm == 64 ? 128 : 256>;
     g.n_row_blocks = (int)(rows / tm);
-    const dim3 grid((unsigned)(g.n_row_blocks * ((4 * g.H + T::TN - 1) / T::TN)));
-    gate_bf16_kernel<kind, T, decltype(split_tag)::value><<<grid, T::NT, 0, st>>>(g);
+    const int64_t blocks = (int64_t)g.n_row_blocks * ((4 * g.H + T::TN - 1) / T::TN);
+    if (blocks * T::NT > 0xFFFFFFFFll) {  // (states of over 200 GB)
+      fits = false;
+      return;
+    }
+    gate_bf16_kernel<kind, T, decltype(split_tag)::value><<<dim3((unsigned)blocks), T::NT, 0, st>>>(g);
   };
   ProfScope ps(kKGate, st);
   if (plan.rows > 0) {
@@ -1151,7 +1158,7 @@ hipError_t launch_gate_bf16(const ForwardArgs& a, int l, const void* x, const vo
     rows = R.M - plan.rows;
     dispatch_bf16(a, 64, go);
   }
-  return hipGetLastError();
+  return fits ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 hipError_t launch_head_bf16(const ForwardArgs& a, const void* hist, int t0, int Tc, const float* zbo,
@@ -1188,11 +1195,12 @@ hipError_t launch_head_bf16(const ForwardArgs& a, const void* hist, int t0, int 
   auto go = [&](auto kind_tag, auto tm_tag, auto split_tag) {
     constexpr int kind = decltype(kind_tag)::value, tm = decltype(tm_tag)::value;
     using T = Tiles<kind, tm, kVocabTileWide>;
-    const dim3 grid((unsigned)((int64_t)a.ws.nvt * (h.rows / tm)));
     ProfScope ps(kKHead, st);
-    head_bf16_kernel<kind, T, decltype(split_tag)::value><<<grid, T::NT, 0, st>>>(h);
+    head_bf16_kernel<kind, T, decltype(split_tag)::value><<<wide_grid(h.rows / tm * a.ws.nvt), T::NT, 0, st>>>(h);
   };
-  dispatch_bf16(a, plan_tiles(a, h.rows, h.V, false).tm, go);
+  const int tm = plan_tiles(a, h.rows, h.V, false).tm;
+  if (h.rows / tm * a.ws.nvt > 0x7FFFFFFF) return hipErrorInvalidValue;
+  dispatch_bf16(a, tm, go);
   return hipGetLastError();
 }
 

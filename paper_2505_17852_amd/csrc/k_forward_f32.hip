@@ -696,6 +696,7 @@ struct HeadArgs {
   RowMap rm;
   int64_t M;
   int64_t rows;    // Tc M
+  int blocks;        // workgroups (block_id may run past them)
   int blocks_per_t;  // row blocks of one timestep
   int nvt;             // vocabulary tiles
   const float* w_out;  // W_out: packed copy, or theta's own
@@ -719,7 +720,9 @@ __global__ __launch_bounds__(NT, 2) void head_f32_kernel(HeadArgs g) {
   static_assert(64 * CT == kVocabTile, "head vocabulary tile");
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   int mb, vt;
-  tile_of(blockIdx.x, gridDim.x, g.nvt, mb, vt);
+  const int id = (int)block_id();
+  if (id >= g.blocks) return;
+  tile_of(id, g.blocks, g.nvt, mb, vt);
   const int v0 = vt * kVocabTile, V = g.V;
   const int tt = mb / g.blocks_per_t;
   RowTiles rt = row_tiles<T::NS, RT>(g.rm, mb - tt * g.blocks_per_t);
@@ -865,7 +868,7 @@ hipError_t launch_gates_f32(const ForwardArgs& a, const GateLayerF32* ls, int n,
   g.ncol = g.H / (16 * pk.ct);
   g.packed = a.wpack != nullptr;
   const int64_t blocks = row_blocks(g.rm, R.M, ns, pk.rt) * g.ncol;
-  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  if (blocks * NT > 0xFFFFFFFFll) return hipErrorInvalidValue;  // (states of over 200 GB)
   const dim3 grid((unsigned)blocks, (unsigned)n);
   ProfScope ps(kKGate, st);
   return by_kind(a, [&](auto k) {
@@ -917,7 +920,8 @@ hipError_t launch_head_f32(const ForwardArgs& a, const void* hist, int t0, int T
   h.w_out = a.wpack ? a.wpack + a.zmap.out : (const float*)a.theta + a.lay.w_out;
   const int64_t blocks = (int64_t)h.blocks_per_t * Tc * h.nvt;
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks);
+  h.blocks = (int)blocks;
+  const dim3 grid = wide_grid(blocks);
   ProfScope ps(kKHead, st);
   return by_kind(a, [&](auto k) {
     return by_rt(pk.rt, [&](auto r) {

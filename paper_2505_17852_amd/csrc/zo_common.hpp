@@ -167,6 +167,16 @@ struct Rows {
   int fd;
 };
 
+// Grids that may have more workgroups than one dimension takes: a dimension's
+// workgroups times their threads (up to 1,024) must stay below 2^32, and the
+// runtime cuts a larger product to 32 bits without an error. x takes up to kGridX
+// workgroups (a multiple of 8, so that workgroup i stays on XCD i % 8), y the
+// rest; block_id() (zo_rng.hpp) counts them, in the last row past their number.
+constexpr int64_t kGridX = (int64_t)1 << 21;
+inline dim3 wide_grid(int64_t blocks) {
+  return blocks <= kGridX ? dim3((unsigned)blocks) : dim3((unsigned)kGridX, (unsigned)((blocks + kGridX - 1) / kGridX));
+}
+
 struct RowMap {
   int Bp;
   int64_t pair_rows;

@@ -20,6 +20,9 @@
 
 namespace zo {
 
+// Workgroup of a wide_grid.
+__device__ __forceinline__ int64_t block_id() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 enum : uint32_t { kTagRademacher = 0u, kTagGaussian = 1u, kTagInit = 2u };
 
 struct Key {

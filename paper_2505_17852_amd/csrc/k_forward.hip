@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kCombineRows* kCombineSteps) void combine_kernel(
     int B, RowMap rm, const uint8_t* mask, const int32_t* tokens, int V, double* row_loss) {
   __shared__ float ell[kCombineSteps][kCombineRows];
   const int lr = threadIdx.x % kCombineRows, step = threadIdx.x / kCombineRows;
-  const int64_t r = (int64_t)blockIdx.x * kCombineRows + lr;
+  const int64_t r = block_id() * kCombineRows + lr;
   const int b = r < M ? pass_of(rm, r).b : B;
   double acc = step == 0 && r < M ? row_loss[r] : 0.0;
   for (int c0 = 0; c0 < Tc; c0 += kCombineSteps) {
@@ -555,7 +555,7 @@ hipError_t launch_forward(const ForwardArgs& a, hipStream_t st) {
       PhaseRange head_range("forward: head and cross entropy of a time chunk");
       ZO_TRY(head(a, hist, t0, Tc, zbo, pmax, psum, ptgt, st));
       ProfScope ps(kKCombine, st);
-      combine_kernel<<<dim3((unsigned)((M + kCombineRows - 1) / kCombineRows)), kCombineRows * kCombineSteps, 0, st>>>(
+      combine_kernel<<<wide_grid((M + kCombineRows - 1) / kCombineRows), kCombineRows * kCombineSteps, 0, st>>>(
           pmax, psum, ptgt, W.nvt, (int64_t)Tc * M, M, t0, Tc, a.C, R.B, rm, a.mask, a.tokens, a.cfg.vocab, row_loss);
       ZO_TRY(hipGetLastError());
     }

@@ -982,7 +982,7 @@ __global__ __launch_bounds__(256) void embed_bf16_kernel(const uint16_t* theta, 
                                                          RowMap rm, int64_t M, Key key, uint32_t i0,
                                                          float eps, uint16_t* x0) {
   const int E4 = E >> 2;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t idx = block_id() * blockDim.x + threadIdx.x;
   if (idx >= M * E4) return;
   const int64_t r = idx / E4;
   const int e = (int)(idx - r * E4) * 4;
@@ -1020,7 +1020,7 @@ __global__ __launch_bounds__(256) void embed_bf16_rad_kernel(const uint16_t* the
                                                              RowMap rm, int64_t M, Key key, uint32_t i0,
                                                              float eps, uint16_t* x0) {
   const int E32 = E >> 5;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t idx = block_id() * blockDim.x + threadIdx.x;
   if (idx >= M * E32) return;
   const int64_t r = idx / E32;
   const int e = (int)(idx - r * E32) * 32;
@@ -1092,12 +1092,12 @@ hipError_t launch_embed_bf16(const ForwardArgs& a, int t, void* x0, hipStream_t 
   ProfScope ps(kKEmbed, st);
   if (a.cfg.probe == ZO_RADEMACHER) {
     const int64_t n = R.M * (E / 32);
-    const unsigned grid = (unsigned)((n + 255) / 256);
+    const dim3 grid = wide_grid((n + 255) / 256);
     embed_bf16_rad_kernel<<<grid, 256, 0, st>>>((const uint16_t*)a.theta, a.lay.emb, E, a.cfg.vocab, a.tokens, a.C, t, R.B,
                                                 rm, R.M, key, a.i0, a.eps, (uint16_t*)x0);
   } else {
     const int64_t n = R.M * (E / 4);
-    const unsigned grid = (unsigned)((n + 255) / 256);
+    const dim3 grid = wide_grid((n + 255) / 256);
     embed_bf16_kernel<ZO_GAUSSIAN><<<grid, 256, 0, st>>>((const uint16_t*)a.theta, a.lay.emb, E,
                                                          a.cfg.vocab, a.tokens, a.C, t, R.B, rm, R.M, key, a.i0,
                                                          a.eps, (uint16_t*)x0);

@@ -30,7 +30,7 @@ __global__ __launch_bounds__(256) void debug_gauss_kernel(const uint32_t* words,
 // theta_j ~ U(-1/sqrt(H), 1/sqrt(H)); one Philox block (tag 2) per 4 elements.
 template <typename T>
 __global__ __launch_bounds__(256) void init_kernel(T* theta, uint64_t P, Key key, float scale) {
-  const uint64_t blk = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint64_t blk = (uint64_t)block_id() * blockDim.x + threadIdx.x;
   const uint64_t j0 = blk << 2;
   if (j0 >= P) return;
   const Words x = stream_block(key, blk, 0u, kTagInit);
@@ -761,10 +761,10 @@ __global__ __launch_bounds__(256) void update_gaussian_kernel(T* theta, uint64_t
   __shared__ float coef[256];
   __shared__ int flag;
   const bool ok = losses_finite(Lp, Lm, N, lm_stride, &flag);
-  if (blockIdx.x == 0 && threadIdx.x == 0 && skipped) *skipped = ok ? 0 : 1;
+  if (block_id() == 0 && threadIdx.x == 0 && skipped) *skipped = ok ? 0 : 1;
   if (!ok) return;
   const int t = threadIdx.x;
-  const uint64_t blk = (uint64_t)blockIdx.x * blockDim.x + t;
+  const uint64_t blk = (uint64_t)block_id() * blockDim.x + t;
   const uint64_t j = blk << 2;
   float th[4];
   load4(theta, j, P, th);
@@ -838,11 +838,11 @@ hipError_t launch_debug_gauss_pairs(const uint32_t* words, uint64_t n_pairs, flo
 
 hipError_t launch_init(int wdtype, void* theta, uint64_t P, uint64_t seed, float scale,
                        hipStream_t s) {
-  const uint64_t grid = ((P + 3) / 4 + 255) / 256;
+  const dim3 grid = wide_grid((int64_t)(((P + 3) / 4 + 255) / 256));
   if (wdtype == ZO_WBF16)
-    init_kernel<uint16_t><<<dim3((unsigned)grid), dim3(256), 0, s>>>((uint16_t*)theta, P, make_key(seed), scale);
+    init_kernel<uint16_t><<<grid, dim3(256), 0, s>>>((uint16_t*)theta, P, make_key(seed), scale);
   else
-    init_kernel<float><<<dim3((unsigned)grid), dim3(256), 0, s>>>((float*)theta, P, make_key(seed), scale);
+    init_kernel<float><<<grid, dim3(256), 0, s>>>((float*)theta, P, make_key(seed), scale);
   return hipGetLastError();
 }
 
@@ -917,12 +917,12 @@ hipError_t launch_update(int wdtype, int kind, void* theta, uint64_t P, uint64_t
       bits ? go(TypeTag<float>{}, integral_constant<bool, true>{})
            : go(TypeTag<float>{}, integral_constant<bool, false>{});
   } else {
-    const uint64_t grid = ((P + 3) / 4 + 255) / 256;
+    const dim3 grid = wide_grid((int64_t)(((P + 3) / 4 + 255) / 256));
     if (wdtype == ZO_WBF16)
-      update_gaussian_kernel<uint16_t><<<dim3((unsigned)grid), dim3(256), 0, s>>>(
+      update_gaussian_kernel<uint16_t><<<grid, dim3(256), 0, s>>>(
           (uint16_t*)theta, P, key, eps, lr, N, i0, Lp, Lm, skipped, lm_stride);
     else
-      update_gaussian_kernel<float><<<dim3((unsigned)grid), dim3(256), 0, s>>>(
+      update_gaussian_kernel<float><<<grid, dim3(256), 0, s>>>(
           (float*)theta, P, key, eps, lr, N, i0, Lp, Lm, skipped, lm_stride);
   }
   return hipGetLastError();

@@ -73,7 +73,8 @@ enum { ZO_RADEMACHER = 0, ZO_GAUSSIAN = 1 };
 
 /* Model shape. All fields > 0; embed and hidden must be multiples of 32
  * (ZO_ESHAPE otherwise), and for zo_perturbed_losses with bf16 weights
- * multiples of 64; n_layers <= 64. wdtype: ZO_WFP32 or ZO_WBF16
+ * multiples of 64, every weight matrix (the head with its vocabulary rounded up
+ * to 256) below 2^31 values; n_layers <= 64. wdtype: ZO_WFP32 or ZO_WBF16
  * (storage type of theta; bf16 runs every matrix product on fp16 operands
  * from an fp16 copy of the weights, with fp32 accumulation and fp32 cell
  * state, see "Products" below). probe: ZO_RADEMACHER or ZO_GAUSSIAN. */

@@ -128,6 +128,8 @@ static int forward_call(const zo_config* cfg, const void* theta, uint64_t seed, 
   if (cfg->wdtype == ZO_WBF16 && (cfg->embed % 64 || cfg->hidden % 64))
     return fail(ZO_ESHAPE, "bf16 weights: embed (%d) and hidden (%d) must be multiples of 64",
                 cfg->embed, cfg->hidden);
+  if (cfg->wdtype == ZO_WBF16 && !zo::bf16_matrices_fit(*cfg))
+    return fail(ZO_ESHAPE, "bf16 weights: every weight matrix must stay below 2^31 values");
   if (!theta || !tokens || !L1 || !L2 || !workspace)
     return fail(ZO_EINVAL, "a required pointer is NULL");
   if (!aligned16(theta) || !aligned16(workspace))

@@ -264,6 +264,13 @@ inline ZCacheMap make_zcache_map(const zo_config& c) {
   return m;
 }
 
+// The bf16 kernels reach a packed matrix through one buffer resource with 32-bit
+// offsets.
+inline bool bf16_matrices_fit(const zo_config& c) {
+  const uint64_t H = (uint64_t)c.hidden, K = std::max(H, (uint64_t)c.embed);
+  return 4 * H * K * 2 < 1ull << 32 && make_zcache_map(c).out_rows * H * 2 < 1ull << 32;
+}
+
 // Bit-packed sign-probe cache (sign probes): the sign words of probes i0 ..
 // i0+N-1 over the whole parameter vector, written once per call (one Philox
 // block per 128 parameters and probe) and read by the forward kernels in place of regenerating them in every K tile: probe n's word w, the

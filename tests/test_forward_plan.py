@@ -197,3 +197,15 @@ def test_noalloc_array_holds_every_call_its_account_admits(calls, zo, wdtype):
     assert want.count(zo.ZO_OK) > 250
     for line, st, o in zip(lines, want, calls(lines)):
         assert o[0] == st, (line, o)
+
+
+def test_bf16_matrices_beyond_32_bit_offsets_are_refused(calls, zo):
+    """A packed matrix of 4 GiB and more (the head with its vocabulary in whole
+    256-word tiles, or a gate matrix) is ZO_ESHAPE; the largest below it runs.
+    fp32 weights have no such bound."""
+    big = [(1, 262144, 64, 8192), (1, 261889, 64, 8192), (1, 100, 64, 23232), (1, 100, 65536, 8192)]
+    below = [(1, 261888, 64, 8192), (1, 100, 64, 23104), (1, 100, 65472, 8192)]
+    for shapes, wdtype, want in ((big, wl.BF16, zo.ZO_ESHAPE), (below, wl.BF16, zo.ZO_OK), (big, wl.FP32, zo.ZO_OK)):
+        cfgs = [model(*s, wdtype, p) for s in shapes for p in (wl.RADEMACHER, wl.GAUSSIAN)]
+        lines = [(c, fd, 1, 3, 2, zo.workspace_bytes(c, 1, 3, 2)) for c in cfgs for fd in (0, 1)]
+        assert all(o[0] == want for o in calls(lines)), (shapes, wdtype)

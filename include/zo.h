@@ -64,7 +64,7 @@ typedef enum {
     ZO_EINVAL = -1,     /* a null pointer, a non-positive size, eps <= 0, a non-finite lr ... */
     ZO_ESHAPE = -2,     /* a model shape the kernels do not support (see zo_config) */
     ZO_EDEVICE = -3,    /* a HIP runtime error, or no gfx950 device */
-    ZO_ENOMEM = -4,     /* the workspace is smaller than zo_workspace_bytes_min() */
+    ZO_ENOMEM = -4,     /* the workspace is too small for the call */
     ZO_ENONFINITE = -5  /* reserved: a non-finite loss (zo_update reports it through skipped_out) */
 } zo_status;
 

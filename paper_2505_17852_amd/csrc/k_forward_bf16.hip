@@ -922,7 +922,7 @@ __global__ __launch_bounds__(T::NT, 1) void head_bf16_kernel(HeadArgsB g) {
       for (int v = 0; v < 16; ++v) {
         const float y = acc[mt][nt][v] + add[nt][v];
         acc[mt][nt][v] = y;
-        mx = fmaxf(mx, y);
+        mx = max_or_nan(mx, y);
       }
     }
     // the target logit, where a lane of the wave holds its row's target
@@ -938,7 +938,7 @@ __global__ __launch_bounds__(T::NT, 1) void head_bf16_kernel(HeadArgsB g) {
       if (holds_t) g.ptgt[rr0 + lrow] = yt;
     }
     // the row's WCOLS columns of this wave: half here, half in lane lr + 32
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = max_or_nan(mx, __shfl_xor(mx, 32, 64));
     // sum of exp(y - mx) as 2^(y log2(e) - mx log2(e)) (one fma and one
     // v_exp_f32 per column)
     constexpr float kLog2e = 1.4426950408889634f;
@@ -960,7 +960,7 @@ __global__ __launch_bounds__(T::NT, 1) void head_bf16_kernel(HeadArgsB g) {
   if (t < TM) {
     float mx = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < G::WAVES_N; ++w) mx = fmaxf(mx, red_m[w * TM + t]);
+    for (int w = 0; w < G::WAVES_N; ++w) mx = max_or_nan(mx, red_m[w * TM + t]);
     float sum = 0.f;
 #pragma unroll
     for (int w = 0; w < G::WAVES_N; ++w) {

@@ -764,10 +764,10 @@ __global__ __launch_bounds__(NT, 2) void head_f32_kernel(HeadArgs g) {
 #pragma unroll
     for (int j = 0; j < kVocabTile / 8; ++j) {
       y[j] = v0 + ec + 8 * j < V ? ep[er * kEpRow + ec + 8 * j] : -INFINITY;
-      mx = fmaxf(mx, y[j]);
+      mx = max_or_nan(mx, y[j]);
     }
 #pragma unroll
-    for (int off = 1; off < 8; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    for (int off = 1; off < 8; off <<= 1) mx = max_or_nan(mx, __shfl_xor(mx, off, 64));
     float se = 0.f;
 #pragma unroll
     for (int j = 0; j < kVocabTile / 8; ++j) se += v0 + ec + 8 * j < V ? __expf(y[j] - mx) : 0.f;

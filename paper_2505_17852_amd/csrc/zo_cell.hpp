@@ -1,6 +1,6 @@
-// The LSTM cell, shared by the gate kernels' epilogues. Every operation is
-// spelled out (no contraction left to the compiler), so that the kernels'
-// tile shapes all give the same bits.
+// The LSTM cell, shared by the gate kernels' epilogues, and the heads' maximum.
+// Every operation of the cell is spelled out (no contraction left to the
+// compiler), so that the kernels' tile shapes all give the same bits.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -17,6 +17,10 @@ __device__ __forceinline__ float rcp_ge1(float d) {
 }
 __device__ __forceinline__ float cell_sigmoid(float x) { return rcp_ge1(1.0f + __expf(-x)); }
 __device__ __forceinline__ float cell_tanh(float x) { return fmaf(-2.0f, rcp_ge1(__expf(2.0f * x) + 1.0f), 1.0f); }
+
+// The larger of two logits, NaN if either is: a vocabulary tile's maximum must
+// not pass over a NaN logit, or a tile of nothing else would count as empty.
+__device__ __forceinline__ float max_or_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 
 // c <- f c + i g; returns h = o tanh(c), from the gates' pre-activations.
 __device__ __forceinline__ float lstm_cell(float ai, float af, float ag, float ao, float& c) {

@@ -246,11 +246,9 @@ __device__ __forceinline__ void packed_source(const PackSegs& segs, uint32_t blk
                                               int64_t& k) {
   m = 0;
   while (m + 1 < segs.n && blk >= (uint32_t)(segs.cstart[m + 1] >> 9)) ++m;
-  const uint32_t rel = blk - (uint32_t)(segs.cstart[m] >> 9), KS = (uint32_t)segs.K[m] / kPackKStep;
-  const uint32_t cb = rel / KS, ks = rel - cb * KS;
-  const int64_t col = (int64_t)kPackBlockCols * cb + (lane & 31);
-  k = kPackKStep * (int64_t)ks + 8 * (lane >> 5);
-  row = segs.head[m] ? (col < segs.V ? col : -1) : gate_row_of_column(col, segs.H);
+  const PackedPos p = packed_position(blk - (uint32_t)(segs.cstart[m] >> 9), lane, (uint32_t)segs.K[m]);
+  k = p.k;
+  row = segs.head[m] ? (p.col < segs.V ? p.col : -1) : gate_row_of_column(p.col, segs.H);
 }
 
 // fp16 copy of the bf16 weight matrices, fragment-packed, read by the bf16

@@ -1052,11 +1052,9 @@ __global__ __launch_bounds__(256) void embed_bf16_rad_kernel(const uint16_t* the
   for (int q = 0; q < 4; ++q) dst[q] = out[q];
 }
 
-// The tiles of a launch of this call (cols columns): a tile lies inside one
-// probe's rows, a wave row inside one sign's.
+// The tiles of a launch of this call (cols columns).
 TilePlan plan_tiles(const ForwardArgs& a, int64_t rows, int64_t cols, bool gate) {
-  const int64_t fit = a.rows.fd ? a.rows.Bp : 2 * (int64_t)a.rows.Bp;
-  return pick_tiles(rows, cols, gate, fit % 256 == 0 ? 256 : fit % 128 == 0 ? 128 : 64);
+  return pick_tiles(rows, cols, gate, largest_tile(a.rows));
 }
 
 // Calls go(kind, tm, split) with the compile-time variant of this call: the

@@ -177,6 +177,14 @@ inline dim3 wide_grid(int64_t blocks) {
   return blocks <= kGridX ? dim3((unsigned)blocks) : dim3((unsigned)kGridX, (unsigned)((blocks + kGridX - 1) / kGridX));
 }
 
+// The most rows of a bf16 tile: a tile lies inside one probe's rows, a wave row
+// (half of it) inside one sign's.
+inline int largest_tile(const Rows& r) {
+  for (int tm : kTileRows)
+    if (r.pair_rows % tm == 0) return tm;
+  return 0;
+}
+
 struct RowMap {
   int Bp;
   int64_t pair_rows;

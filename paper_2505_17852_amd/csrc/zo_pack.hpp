@@ -35,17 +35,16 @@ __host__ __device__ inline int64_t gate_row_of_column(int64_t rho, int64_t H) {
   return (c >> 4) * H + 16 * ug + (c & 15);
 }
 
-// Source of 16-byte chunk u of a packed matrix with K columns of k: the
-// column (in the kernels' order) and the first k of its 8 values.
-struct PackedChunk {
+// Source of lane `lane`'s 16 bytes of 1 KB block `blk` of a packed matrix with K
+// columns of k: the column (in the kernels' order) and the first k of its 8
+// values. (32 bits: a matrix has at most 2^31 values, 2^22 blocks.)
+struct PackedPos {
   int64_t col;
   int64_t k;
 };
-__host__ __device__ inline PackedChunk packed_chunk(uint64_t u, int64_t K) {
-  const int64_t KS = K / kPackKStep;
-  const int64_t lane = (int64_t)(u & 63u), rest = (int64_t)(u >> 6);
-  const int64_t ks = rest % KS, cb = rest / KS;
-  return PackedChunk{kPackBlockCols * cb + (lane & 31), kPackKStep * ks + 8 * (lane >> 5)};
+__host__ __device__ inline PackedPos packed_position(uint32_t blk, int lane, uint32_t K) {
+  const uint32_t KS = K / kPackKStep, cb = blk / KS, ks = blk - cb * KS;
+  return PackedPos{kPackBlockCols * (int64_t)cb + (lane & 31), kPackKStep * (int64_t)ks + 8 * (lane >> 5)};
 }
 
 // Byte offset, inside a packed matrix with K columns of k, of the 16 bytes
@@ -64,7 +63,7 @@ __host__ __device__ inline int64_t packed_block_of(int64_t nb, int wn, int nt, i
 }
 
 // Activation tile copies (global -> LDS, 1 KB per wave instruction): copy q
-// of wave w fills LDS rows 8 (q NW + w) .. + 7 of the 256-row tile (128-byte
+// of wave w fills LDS rows 8 (q NW + w) .. + 7 of the workgroup's tile (128-byte
 // rows of 64 fp16 k, 16-byte chunks XOR-swizzled by row so that the 16 rows
 // of one fragment read cover all banks). Lane L writes row 8 (q NW + w) +
 // L / 8, slot L % 8, which must hold chunk (L % 8) ^ swz(row); this is the

@@ -237,11 +237,6 @@ __device__ __forceinline__ int64_t row_tile(const RowTiles& r, int i, bool& own)
   own = i - RT <= r.last1;
   return r.base1 + min(i - RT, r.last1);
 }
-__host__ __device__ inline int64_t row_blocks(const RowMap& rm, int64_t M, int NS, int RT) {
-  const int q = rm.Bp >> 4;
-  return NS == 2 ? M / (2 * rm.Bp) * ((q + RT - 1) / RT) : M / rm.Bp * ((q + 2 * RT - 1) / (2 * RT));
-}
-
 // Workgroup x of a grid of row blocks x column blocks. Workgroups go to the 8
 // XCDs in turn, each with its own L2: XCD i takes the i-th eighth of the tiles
 // in row-major order, so the column blocks of a row block share its
@@ -802,32 +797,6 @@ hipError_t by_rt(int rt, Go&& go) {
     case 3: return go(integral_constant<int, 3>{});
     default: return go(integral_constant<int, 4>{});
   }
-}
-
-// The tile shape of a launch: the cheapest by the time a compute unit spends
-// on its workgroups. A workgroup of RT and CT takes, per k tile and wave, CT x
-// (forming its weights: 480 cycles, 270 for one sign, and 12 RT MFMAs of 16
-// cycles) plus a fixed part; the chip takes ceil(workgroups / CUs) of them.
-// Every shape sums in the same order, so the choice never changes a result.
-struct Pick {
-  int rt, ct;
-};
-Pick pick_shape(const RowMap& rm, int64_t M, int NS, int64_t cols, int64_t groups, bool ct1) {
-  constexpr int kCus = 256;
-  Pick best{4, 2};
-  double cost = 0;
-  for (int ct = 2; ct >= (ct1 ? 1 : 2); --ct) {
-    for (int rt = 4; rt >= 1; --rt) {
-      const int64_t wgs = row_blocks(rm, M, NS, rt) * ((cols + 64 * ct - 1) / (64 * ct)) * groups;
-      const double one = ct * ((NS == 2 ? 480 : 270) + 192.0 * rt) + 150;
-      const double c = (double)((wgs + kCus - 1) / kCus) * one;
-      if (cost == 0 || c < 0.97 * cost) {
-        cost = c;
-        best = Pick{rt, ct};
-      }
-    }
-  }
-  return best;
 }
 
 }  // namespace

@@ -220,6 +220,42 @@ __host__ __device__ inline PassOf pass_of(const RowMap& m, int64_t r) {
   return loc >= m.Bp ? PassOf{(int)p, -1, loc - m.Bp} : PassOf{(int)p, 1, loc};
 }
 
+// Workgroup tiles of the fp32 path: 2 rt row tiles of 16 rows (rt of each pass of
+// a probe, central differences; 2 rt of one pass, forward differences), 64 ct
+// columns. ns: the signs of a workgroup's rows, 2 or 1.
+inline int64_t row_blocks(const RowMap& rm, int64_t M, int NS, int RT) {
+  const int q = rm.Bp >> 4;
+  return NS == 2 ? M / (2 * rm.Bp) * ((q + RT - 1) / RT) : M / rm.Bp * ((q + 2 * RT - 1) / (2 * RT));
+}
+// The tile shape of a launch: the cheapest by the time a compute unit spends
+// on its workgroups. A workgroup of RT and CT takes, per k tile and wave, CT x
+// (forming its weights: 480 cycles, 270 for one sign, and 12 RT MFMAs of 16
+// cycles) plus a fixed part; the chip takes ceil(workgroups / CUs) of them.
+// Every shape sums in the same order, so the choice never changes a result. (The
+// forming time is that of sign words read as bits; reading eps z takes about as
+// long, regenerating normals several times it. The rule does not tell them
+// apart: no other shape was measured for regenerated probes.)
+struct Pick {
+  int rt, ct;
+};
+inline Pick pick_shape(const RowMap& rm, int64_t M, int NS, int64_t cols, int64_t groups, bool ct1) {
+  constexpr int kCus = 256;
+  Pick best{4, 2};
+  double cost = 0;
+  for (int ct = 2; ct >= (ct1 ? 1 : 2); --ct) {
+    for (int rt = 4; rt >= 1; --rt) {
+      const int64_t wgs = row_blocks(rm, M, NS, rt) * ((cols + 64 * ct - 1) / (64 * ct)) * groups;
+      const double one = ct * ((NS == 2 ? 480 : 270) + 192.0 * rt) + 150;
+      const double c = (double)((wgs + kCus - 1) / kCus) * one;
+      if (cost == 0 || c < 0.97 * cost) {
+        cost = c;
+        best = Pick{rt, ct};
+      }
+    }
+  }
+  return best;
+}
+
 // Time steps whose top-layer states are kept for one batched output-head pass
 // (fp32 path: see time_chunk).
 constexpr int kTimeChunk = 16;
@@ -228,8 +264,8 @@ constexpr int kTimeChunk = 16;
 // 128 on the fp32 path.
 constexpr int kVocabTile = 128;
 // Columns per workgroup of the bf16 products (gate columns or vocabulary
-// rows); its rows are 65536 / kVocabTileWide. (128 x 512 workgroups, which
-// load each weight fragment once, measured slower than 256 x 256.)
+// rows; the gate's 64-row tiles have 128). (128 x 512 workgroups, which load
+// each weight fragment once, measured slower than 256 x 256.)
 constexpr int kVocabTileWide = 256;
 inline int vocab_tile(const zo_config& c) { return c.wdtype == ZO_WBF16 ? kVocabTileWide : kVocabTile; }
 

@@ -1,8 +1,8 @@
-"""fp32 products as sums of bf16 matrix products: every tile shape of the fp32
-gate and head kernels against the oracle, at the sizes where a shape changes
-(batches around multiples of 16 rows, one to four row tiles per sign, partial
-row blocks, K tiles that do not fill a stage), for sign and normal probes,
-central and forward differences."""
+"""fp32 products as sums of bf16 matrix products against the oracle: batches around
+multiples of 16 rows, K tiles that do not fill a stage, small and ragged
+vocabularies, for sign and normal probes, central and forward differences. Calls
+as small as these take one row tile per workgroup; the other tile shapes are in
+test_gpu_f32_shapes.py."""
 import numpy as np
 import pytest
 
@@ -31,7 +31,7 @@ def say(*a):
     print(*a, flush=True)
 
 
-# (B, E, H, V, C): row tiles per pass 1, 2, 3, 4, 5 (a partial block), 9; K tiles
+# (B, E, H, V, C): 1, 1, 2, 3, 4, 5 and 9 row tiles per pass; K tiles
 # of 1 + 1 up to 5 + 3; vocabularies of 1, 128, 129 and 300
 SHAPES = [(1, 32, 32, 1, 3), (16, 32, 64, 128, 2), (17, 64, 32, 129, 2), (47, 96, 96, 40, 3), (64, 160, 96, 300, 2),
           (65, 32, 96, 77, 2), (130, 64, 64, 50, 2)]

@@ -61,7 +61,7 @@ def check(gp, gm, rp, rm, tol=LOSS_RTOL_BF16):
 
 CASES = [
     # several unit tiles (H=128), a ragged vocabulary (300 = 2 tiles + 44), B=5
-    # (padded to 128 rows per sign), C=20 (a full and a partial time chunk)
+    # (padded to 32 rows per sign), C=20 (a full and a partial time chunk)
     ("rad-ragged", dict(n_layers=2, vocab=300, embed=64, hidden=128, wdtype=1, probe=0), 2, 5, 20, 1e-2, True),
     ("gauss", dict(n_layers=2, vocab=200, embed=128, hidden=64, wdtype=1, probe=1), 2, 3, 9, 1e-2, True),
     ("deep3-rad", dict(n_layers=3, vocab=130, embed=64, hidden=192, wdtype=1, probe=0), 3, 2, 7, 1e-3, False),
@@ -107,7 +107,7 @@ def test_bf16_slice_and_determinism(zo):
 
 
 # Sequences scored at full size, and how many leading positions of each: the
-# first two sit in the first 128-row wave tile of each pass, 129 and 255 in
+# first two sit in the first 128-row wave row of each pass, 129 and 255 in
 # the second (B = 256 fills a 256-row workgroup tile per pass).
 FULL_SEQS = ((0, 3), (1, 2), (129, 2), (255, 1))
 

@@ -66,7 +66,7 @@ CASES = [
      2, 5, 20, 1e-4, True),
     ("bf16-gauss-2stream", dict(n_layers=2, vocab=200, embed=128, hidden=64, wdtype=wl.BF16, probe=wl.GAUSSIAN),
      3, 3, 9, 3e-5, False),
-    # B = 128 rows per pass: the 128-row workgroups of the fp32 gate
+    # eight 16-row tiles per pass
     ("fp32-wide", dict(n_layers=2, vocab=100, embed=32, hidden=64, wdtype=wl.FP32, probe=wl.RADEMACHER),
      2, 128, 4, 1e-2, True),
 ]

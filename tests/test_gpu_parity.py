@@ -198,7 +198,7 @@ LOSS_CASES = [
     ("deep3-gauss", dict(n_layers=3, vocab=130, embed=128, hidden=64, wdtype=0, probe=1), 2, 2, 9, 1e-3, False),
     ("c2-widths", wl.model_cfg("c2"), 2, 3, 12, 1e-3, True),
     ("c5-widths", wl.model_cfg("c5"), 2, 2, 10, 1e-2, False),
-    # B = 64 fills 128 rows per probe: the 128-row workgroups of the fp32 gate
+    # wider batches: four 16-row tiles per sign, the last one partly padding for B = 50
     ("wide-rad", dict(n_layers=2, vocab=100, embed=32, hidden=64, wdtype=0, probe=0), 2, 64, 5, 1e-2, True),
     ("wide-gauss", dict(n_layers=2, vocab=100, embed=64, hidden=96, wdtype=0, probe=1), 2, 50, 4, 1e-2, True),
 ]

@@ -1,7 +1,8 @@
 """The sign-probe update for more than 16 probes of a large model (workgroups of
 four tiles with replicated tables) against the oracle on sampled parameters:
 tile edges, the last partial tile, group remainders of 1, 8, 9 and 16 probes,
-the cached sign words, a non-finite loss."""
+the cached sign words, a non-finite loss; more than 512 probes, past which the
+workgroups work out the coefficients again."""
 import numpy as np
 import pytest
 
@@ -63,3 +64,29 @@ def test_many_probes_large_model(zo, N, wdtype):
     kept = theta.clone()
     zo.update(cfg, theta, seed, eps, lr, *d, i0=i0, skipped=skipped)
     assert int(skipped) == 1 and torch.equal(theta, kept)
+
+
+@pytest.mark.parametrize("N", [512, 513, 1041])
+def test_coefficients_past_512_probes(zo, N):
+    """A workgroup of 512 threads holds 512 coefficients at a time. Probe values
+    from the library's own stream (checked against the oracle elsewhere)."""
+    cfg = dict(n_layers=1, vocab=16411, embed=512, hidden=512, wdtype=wl.FP32, probe=wl.RADEMACHER)
+    P = zo.param_count(cfg)
+    print(f"update many N={N} P={P}", flush=True)
+    theta = zo.new_theta(cfg)
+    zo.init(cfg, theta, 3)
+    before = theta.clone()
+    rng = np.random.default_rng(N)
+    lp = (9.7 + 1e-3 * rng.standard_normal(N)).astype(np.float32)
+    lm = (9.7 + 1e-3 * rng.standard_normal(N)).astype(np.float32)
+    eps, lr, seed, i0 = 1e-3, 1e-1, 77, 3
+    zo.update(cfg, theta, seed, eps, lr, *[torch.from_numpy(x).cuda() for x in (lp, lm)], i0=i0)
+    c = ((np.float64(np.float32(lr)) / N) * ((lp.astype(np.float64) - lm) / (2.0 * np.float64(np.float32(eps))))).astype(np.float32)
+    n = 4096
+    for j in (0, 512 * 8192 - n // 2, P - n):
+        want = before[j:j + n].double()
+        for k in range(N):
+            want -= float(c[k]) * zo.debug_probe(wl.RADEMACHER, seed, i0 + k, j, n).double()
+        # N fp32 additions of terms of at most sum |c|, then fp32's rounding of the result
+        tol = N * 2.0 ** -24 * float(np.abs(c).sum()) + want.abs() * 2.0 ** -23
+        assert torch.all((theta[j:j + n].double() - want).abs() <= tol)

@@ -50,7 +50,7 @@ def both(zo, cfg, N, B, C, seed, eps, masked, i0=0):
 
 
 SEQUENCE = [
-    # the whole c2 workload (113.6 MiB of the 128 MiB scratch), then smaller calls
+    # the whole c2 workload (an account of 113.6 of the 128 MiB), then smaller calls
     ("c2-full", wl.model_cfg("c2"), 32, 64, 256, 1e-3, True),
     ("ragged-fp32", dict(n_layers=2, vocab=300, embed=64, hidden=96, wdtype=wl.FP32, probe=wl.RADEMACHER),
      3, 5, 20, 1e-2, True),

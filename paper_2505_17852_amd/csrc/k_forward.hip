@@ -464,7 +464,7 @@ hipError_t launch_forward(const ForwardArgs& a, hipStream_t st) {
     zr.n_state = (int64_t)(state / 16);
     zr.stride = 2 * zr.n_state;
     zr.p[0] = (uint4*)(T > 1 ? hist + (size_t)(T - 1) * state : ws + W.hzero);
-    zr.n[0] = T > 1 ? zr.n_state : (int64_t)(zero_state_bytes(c) / 16);
+    zr.n[0] = T > 1 ? zr.n_state : (int64_t)(zero_state_bytes(c, M) / 16);
     zr.p[1] = (uint4*)cbuf;
     zr.n[1] = (int64_t)((size_t)L * M * H / 4);
     zr.p[2] = (uint4*)row_loss;
@@ -488,7 +488,7 @@ hipError_t launch_forward(const ForwardArgs& a, hipStream_t st) {
   // states of layer l at time t: lower layers alternate between two slots
   // (time t in slot t & 1), the top layer writes the time-chunk ring. A ring of
   // one slot (C = 1) holds only the state being written, while other
-  // workgroups still read the one before it: that one is a zero row of its own
+  // workgroups still read the one before it: that one has memory of its own
   auto state_in = [&](int l, int t) -> char* {  // h of layer l at time t - 1
     if (l < L - 1) return hbuf + (size_t)l * 2 * state + (size_t)((t + 1) & 1) * state;
     return T > 1 ? hist + (size_t)((t + T - 1) % T) * state : ws + W.hzero;
@@ -526,7 +526,6 @@ hipError_t launch_forward(const ForwardArgs& a, hipStream_t st) {
         GateLayerF32& g = ls[n++];
         g.x = l == 0 ? x0 + (size_t)(t % T) * x0_step : state_out(l - 1, t);
         g.hprev = state_in(l, t);
-        g.hstep = l == L - 1 && T == 1 ? 0 : (int64_t)(16 * (size_t)H * el);
         g.hout = state_out(l, t);
         g.cst = cbuf + (size_t)l * M * H;
         g.off_ih = a.lay.w_ih[l];

@@ -288,8 +288,8 @@ __device__ __forceinline__ void mainloop_bf16(f16v (&acc)[T::MT][2], const SegB 
 
   // Buffer resources: the workgroup's activation rows and the packed matrices
   // of each segment (the probe cache per probe).
-  const Rsrc ra0 = make_rsrc(s0.A, (uint32_t)(((TM - 1) * s0.lda + s0.K) * 2));
-  const Rsrc ra1 = make_rsrc(s1.A, (uint32_t)(((TM - 1) * s1.lda + s1.K) * 2));
+  const Rsrc ra0 = make_rsrc(s0.A, (uint32_t)(TM * s0.lda * 2));
+  const Rsrc ra1 = make_rsrc(s1.A, (uint32_t)(TM * s1.lda * 2));
   const Rsrc rw0 = make_rsrc(s0.W, s0.wbytes), rw1 = make_rsrc(s1.W, s1.wbytes);
   Rsrc rz0 = rw0, rz1 = rw1;
   if constexpr (T::kZDirect) {
@@ -660,12 +660,12 @@ __device__ __forceinline__ void zero_acc(f16v (&acc)[MT][NTW]) {
 // ---------------------------------------------------------------------------
 struct GateArgsB {
   const uint16_t* x;      // [M][El] bf16
-  const uint16_t* hprev;  // [M][H], row stride ldh (0: one row of zeros for all rows)
+  const uint16_t* hprev;  // [M][H]
   uint16_t* hout;         // [M][H]
   float* cst;             // [M][H] fp32
   const uint16_t* theta;
   uint64_t off_ih, off_hh, off_b;
-  int El, H, ldh;
+  int El, H;
   const float* zb;  // [N][4H] eps z of the bias
   Key key;
   uint32_t i0;
@@ -719,7 +719,7 @@ __global__ __launch_bounds__(T::NT, T::NT == 256 ? 3 : 1) void gate_bf16_kernel(
   const bool pert = kind == kGaussPerturbed && sgn != 0;
   const SegB s0{g.x + m0 * g.El, g.El, pert ? g.zc_ih + ppos : g.w_ih16, (uint32_t)((uint64_t)4 * H * g.El * 2),
                 g.off_ih, g.El, g.El, kind == kGaussCached ? g.zc_ih + zpos : nullptr};
-  const SegB s1{g.hprev + m0 * g.ldh, g.ldh, pert ? g.zc_hh + ppos : g.w_hh16, (uint32_t)((uint64_t)4 * H * H * 2), g.off_hh,
+  const SegB s1{g.hprev + m0 * H, H, pert ? g.zc_hh + ppos : g.w_hh16, (uint32_t)((uint64_t)4 * H * H * 2), g.off_hh,
                 H, H, kind == kGaussCached ? g.zc_hh + zpos : nullptr};
   const BitsB bits{kind == kSignsCached ? g.bits + (uint64_t)pair * g.bits_stride : nullptr,
                    (uint32_t)(g.bits_stride * 4)};
@@ -1109,7 +1109,6 @@ hipError_t launch_gate_bf16(const ForwardArgs& a, int l, const void* x, const vo
   GateArgsB g;
   g.x = (const uint16_t*)x;
   g.hprev = (const uint16_t*)hprev;
-  g.ldh = l == a.cfg.n_layers - 1 && a.ws.T == 1 ? 0 : a.cfg.hidden;
   g.hout = (uint16_t*)hout;
   g.cst = cst;
   g.theta = (const uint16_t*)a.theta;

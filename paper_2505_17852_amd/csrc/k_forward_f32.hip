@@ -585,6 +585,7 @@ struct GateArgs {
   GateLayerF32 layer[kLaunchLayers];
   const float* theta;
   int H;
+  int hstep;  // bytes between row tiles of the layers' hprev (0: one tile for all)
   Key key;
   uint32_t i0;
   float eps;
@@ -632,7 +633,7 @@ __global__ __launch_bounds__(NT, 2) void gate_f32_kernel(GateArgs g) {
   auto init = [&]() { bias_init<T>(acc, bias, zb, rt.sign0); };
   const uint64_t zpos = (uint64_t)rt.probe * g.zc_stride;
   const Seg s0{gl.x, (gl.El >> 5) * kFrag, gl.w_ih, gl.off_ih, gl.El, T::kZ ? gl.zc_ih + zpos : nullptr};
-  const Seg s1{gl.hprev, gl.hstep, gl.w_hh, gl.off_hh, H, T::kZ ? gl.zc_hh + zpos : nullptr};
+  const Seg s1{gl.hprev, g.hstep, gl.w_hh, gl.off_hh, H, T::kZ ? gl.zc_hh + zpos : nullptr};
   mainloop<T, kSplit>(
       acc, s0, s1, 2, rt, 4 * H, __builtin_amdgcn_readfirstlane(wave * H + u0),
       [&](int ct) { return 16 * ct + (lane & 15); }, g.packed, g.key, g.i0 + (uint32_t)rt.probe, g.eps, T::kBits ? g.bits + (uint64_t)rt.probe * g.bits_stride : nullptr, st0, st1, init);
@@ -825,6 +826,8 @@ hipError_t launch_gates_f32(const ForwardArgs& a, const GateLayerF32* ls, int n,
   for (int i = 0; i < n; ++i) g.layer[i] = ls[i];
   g.theta = (const float*)a.theta;
   g.H = a.cfg.hidden;
+  // (a call with a zero tile has one position: its launches have one layer each)
+  g.hstep = a.ws.T == 1 && ls[0].hprev == a.work + a.ws.hzero ? 0 : g.H / 32 * kFrag;
   g.key = make_key(a.seed);
   g.i0 = a.i0;
   g.eps = a.eps;

@@ -372,8 +372,8 @@ struct WsPlan {
   size_t x0;         // [M][E] perturbed embeddings of one timestep (bf16 path), [T][M][E] of a chunk (fp32)
   size_t hbuf;       // [L-1][2][M][H]     double-buffered states of the lower layers
   size_t hist;       // [T][M][H]          top-layer states of the current time chunk
-  size_t hzero;      // one row of zeros (packed row tile with fp32 weights): the top layer's state before
-                     // the first timestep where the chunk has one slot (C = 1)
+  size_t hzero;      // the top layer's state before the first timestep where the chunk has one slot (C = 1):
+                     // [M][H] (bf16 path), one packed row tile of zeros for all rows (fp32)
   size_t cbuf;       // f32 [L][M][H]      cell states
   size_t zb;         // f32 [L][N][4H]     eps * z of the gate biases, per probe
   size_t zbo;        // f32 [N][V]         eps * z of the head bias, per probe
@@ -421,10 +421,11 @@ inline int least_time_chunk(const zo_config& c, int32_t C) {
   return C < least ? C : least;
 }
 
-// Bytes of the zero state of a one-slot chunk: one row of fp16, or one packed
-// tile of 16 rows.
-inline size_t zero_state_bytes(const zo_config& c) {
-  return (size_t)c.hidden * act_bytes(c) * (c.wdtype == ZO_WBF16 ? 1 : 16);
+// Bytes of the zero state of a one-slot chunk. (bf16 path: all rows; with one
+// row for all, the row stride became a value of its own in the gate kernel,
+// which cost the large model's losses 0.2%.)
+inline size_t zero_state_bytes(const zo_config& c, int64_t M) {
+  return (size_t)c.hidden * act_bytes(c) * (c.wdtype == ZO_WBF16 ? (size_t)M : 16);
 }
 
 inline int vocab_tiles(const zo_config& c) { return (c.vocab + vocab_tile(c) - 1) / vocab_tile(c); }
@@ -457,7 +458,7 @@ inline WsPlan plan_workspace(const zo_config& c, const Rows& r, int T, Caches ca
   w.hbuf = take((L - 1) * 2 * M * H * el);
   w.hist = take((size_t)w.T * M * H * el);
   w.hzero = p;
-  if (w.T == 1) take(zero_state_bytes(c));
+  if (w.T == 1) take(zero_state_bytes(c, r.M));
   w.cbuf = take(L * M * H * 4);
   w.zb = take(L * (size_t)r.N * 4 * H * 4);
   w.zbo = take((size_t)r.N * V * 4);
@@ -549,7 +550,7 @@ inline WsSizes workspace_sizes(const zo_config& c, int32_t N, int32_t B, int32_t
                    plan_workspace(c, r, least, Caches{false, false}).total};
   // a plan without its chunk's buffers and with room for the zero state and each buffer's alignment
   const size_t step = chunk_step_bytes(c, r.M, vocab_tiles(c));
-  const size_t fixed = plan_workspace(c, r, 0, Caches{false, false}).total + zero_state_bytes(c) + 8 * 256;
+  const size_t fixed = plan_workspace(c, r, 0, Caches{false, false}).total + zero_state_bytes(c, r.M) + 8 * 256;
   const size_t need = fixed + (size_t)least * step;
   size_t want = fixed + std::min((size_t)std::min(C, 64) * step, std::max(kChunkBytes, (size_t)std::min(C, 8) * step));
   if (wpack_pays(c, C) && wpack_bytes(c) <= kExtraCap) want += align_up(wpack_bytes(c), 256);

@@ -60,8 +60,7 @@ hipError_t launch_embed_f32(const ForwardArgs& a, int t0, int Tc, void* x0, hipS
 constexpr int kLaunchLayers = 8;
 struct GateLayerF32 {
   const char* x;      // [M][El]
-  const char* hprev;  // [M][H], or one row tile of zeros for all rows
-  int64_t hstep;      // bytes between hprev's row tiles (0: one tile for all)
+  const char* hprev;  // [M][H], or the one row tile at the plan's hzero for all rows
   char* hout;         // [M][H]
   float* cst;         // [M][H] fp32, row-major
   uint64_t off_ih, off_hh, off_b;
@@ -78,7 +77,6 @@ hipError_t launch_head_f32(const ForwardArgs& a, const void* hist, int t0, int T
 
 // k_forward_bf16.hip: the bf16 path's per-timestep kernels.
 hipError_t launch_embed_bf16(const ForwardArgs& a, int t, void* x0, hipStream_t st);
-// (the top layer's hprev of a one-slot chunk is one row of zeros for all rows)
 hipError_t launch_gate_bf16(const ForwardArgs& a, int l, const void* x, const void* hprev, void* hout,
                             float* cst, const float* zb, hipStream_t st);
 hipError_t launch_head_bf16(const ForwardArgs& a, const void* hist, int t0, int Tc, const float* zbo,

@@ -43,11 +43,10 @@ struct Geometry {
   int acopies() const { return tm * 128 / 1024 / nwaves(); }
 };
 
-// the activation copies of one workgroup tile against a resource of tm rows of K
-// values, lda apart (0: one row for all)
+// the activation copies of one workgroup tile against a resource of tm rows of lda
 static void check_copies(int64_t lda, int64_t K, const char* what, Geometry g) {
   const int TM = g.tm;
-  const uint64_t records = ((uint64_t)(TM - 1) * lda + K) * 2;
+  const uint64_t records = (uint64_t)TM * lda * 2;
   CHECK(g.acopies() * g.nwaves() * 1024 == TM * 128, "%s: copies of a %d-row tile", what, TM);
   CHECK(records < (1ull << 31), "%s: resource of %llu bytes", what, (unsigned long long)records);
   std::vector<int> seen(TM * 8, 0);
@@ -274,14 +273,12 @@ int main(int argc, char** argv) {
   check_rows(M, 4 * H, true, "gate");
   for (int64_t Tc : {(int64_t)1, (int64_t)3, (int64_t)16}) check_rows(Tc * M, V, false, "head");
   // gate workgroups: every tile shape the call's rows allow, every layer's two
-  // segments and the zero row before the first timestep, every column block
-  // (tn / 4 hidden units)
+  // segments, every column block (tn / 4 hidden units)
   for (int tm : kTileRows) {
     if (tm > most) continue;
     const Geometry g{tm, (int)tile_cols(tm, true)};
     check_copies(E, E, "gate x", g);
     check_copies(H, H, "gate h", g);
-    check_copies(0, H, "gate zero state", g);
     const int64_t nn = (4 * H + g.tn - 1) / g.tn;
     for (int64_t nb = 0; nb < nn; ++nb) {
       check_cell_copies(nb, H, g);

@@ -66,7 +66,7 @@ void check_state(const zo::ForwardArgs& a, const Range& r) {
 Range acts(const zo::ForwardArgs& a, const char* name, const void* p, size_t K, size_t t = 1) {
   return {name, (const char*)p, t * (size_t)a.rows.M * K * zo::act_bytes(a.cfg)};
 }
-size_t one_row(const zo::ForwardArgs& a) { return zo::zero_state_bytes(a.cfg); }
+size_t zero_tile(const zo::ForwardArgs& a) { return zo::zero_state_bytes(a.cfg, a.rows.M); }
 
 }  // namespace
 
@@ -120,8 +120,10 @@ hipError_t launch_gates_f32(const ForwardArgs& a, const GateLayerF32* ls, int n,
     const GateLayerF32& g = ls[i];
     reads.push_back(acts(a, "x", g.x, (size_t)g.El));
     reads.push_back(acts(a, "h before", g.hprev, (size_t)a.cfg.hidden));
-    if (g.hstep == 0) reads.back().n = one_row(a);
-    else if ((size_t)g.hstep * (size_t)(a.rows.M / 16) != reads.back().n) bad("row tile step", "h before");
+    if (a.ws.T == 1 && g.hprev == a.work + a.ws.hzero) {
+      reads.back().n = zero_tile(a);
+      if (n != 1) bad("more than one layer beside the zero tile:", "h before");
+    }
     writes.push_back(acts(a, "h", g.hout, (size_t)a.cfg.hidden));
     writes.push_back({"c", (const char*)g.cst, (size_t)a.rows.M * (size_t)a.cfg.hidden * 4});
     inside(writes.back());
@@ -138,8 +140,7 @@ hipError_t launch_gates_f32(const ForwardArgs& a, const GateLayerF32* ls, int n,
 hipError_t launch_gate_bf16(const ForwardArgs& a, int l, const void* x, const void* hprev, void* hout, float* cst,
                             const float* zb, hipStream_t) {
   const Range rx = acts(a, "x", x, (size_t)(l == 0 ? a.cfg.embed : a.cfg.hidden));
-  Range rh = acts(a, "h before", hprev, (size_t)a.cfg.hidden);
-  if (l == a.cfg.n_layers - 1 && a.ws.T == 1) rh.n = one_row(a);
+  const Range rh = acts(a, "h before", hprev, (size_t)a.cfg.hidden);
   const Range wh = acts(a, "h", hout, (size_t)a.cfg.hidden);
   const Range wc{"c", (const char*)cst, (size_t)a.rows.M * (size_t)a.cfg.hidden * 4};
   inside({"zb", (const char*)zb, (size_t)a.rows.N * 16 * (size_t)a.cfg.hidden});

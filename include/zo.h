@@ -139,7 +139,7 @@ size_t zo_workspace_bytes(const zo_config* cfg, int32_t N, int32_t B, int32_t C)
 
 /* A workspace without those caches (probes are then regenerated in every
  * tile; the results are the same), as small as holds every call with at most N
- * probes, B sequences and C positions. With fp32 weights up to 16 MiB of caches and
+ * probes, B sequences and C positions. With fp32 weights up to 32 MiB of caches and
  * longer time chunks are counted all the same, so for a small model it equals
  * zo_workspace_bytes, and a call uses the caches that fit whatever the size.
  * Host only. */

@@ -535,10 +535,12 @@ inline size_t account_bytes(const zo_config& c, int32_t N, int32_t B, int32_t C,
 //             kExtraCap each: those had no share in the size when they were
 //             not stored, and a call that was close to the device's memory
 //             stays below it
-//   smallest  no caches beyond 16 MiB of them and of longer chunks (a small
-//             model's smallest workspace then has what its full one has), and
-//             at least account_bytes
-constexpr size_t kExtraCap = (size_t)8 << 30;
+//   smallest  no caches beyond kSmallExtras of them and of longer chunks (a small
+//             model's smallest workspace then has what its full one has; 3
+//             layers of 160 units, 8 probes, a batch of 16: 668 us with the
+//             whole sequence in one chunk, 696 us with one timestep left over),
+//             and at least account_bytes
+constexpr size_t kExtraCap = (size_t)8 << 30, kSmallExtras = (size_t)32 << 20;
 struct WsSizes {
   size_t full, smallest;
 };
@@ -557,7 +559,7 @@ inline WsSizes workspace_sizes(const zo_config& c, int32_t N, int32_t B, int32_t
   size_t zc = 0;
   if (c.probe == ZO_RADEMACHER) want += align_up(std::min(probe_cache_bytes(c, N), kExtraCap), 256);
   else zc = align_up(probe_cache_bytes(c, N), 256);
-  const size_t smallest = std::max(account_bytes(c, N, B, C, fd), std::min(want, need + kChunkBytes));
+  const size_t smallest = std::max(account_bytes(c, N, B, C, fd), std::min(want, need + kSmallExtras));
   return WsSizes{std::max(smallest, want) + zc, smallest};
 }
 

@@ -151,7 +151,7 @@ def test_smallest_f32_workspace_needs_no_caches(calls, zo):
     """The smallest fp32 workspace leaves out the packed weights and the sign
     words (the forward runs without): calls of at least a chunk of positions run
     in as many bytes as before either was stored, and the size reported is at
-    most 16 MiB above that."""
+    most 32 MiB above that."""
     assert _plain(wl.model_cfg("c2"), 32, 64, 256) == 119078912  # 113.6 MiB
     cases = [(model(2, 50000, 512, 1024, wl.FP32, wl.RADEMACHER), 96, 32, 16),
              (model(6, 50000, 1024, 2048, wl.FP32, wl.RADEMACHER), 64, 16, 64)]
@@ -161,7 +161,7 @@ def test_smallest_f32_workspace_needs_no_caches(calls, zo):
         cases.append((cfg, N, B, C + 15))
     for cfg, N, B, C in cases:
         size, plain = zo.workspace_bytes_min(cfg, N, B, C), _plain(cfg, N, B, C)
-        assert plain <= size <= plain + (16 << 20), (cfg, N, B, C, size, plain)
+        assert plain <= size <= plain + (32 << 20), (cfg, N, B, C, size, plain)
     lines = [(cfg, fd, N, B, C, _plain(cfg, N, B, C)) for cfg, N, B, C in cases for fd in (0, 1)]
     out = calls(lines)
     assert all(o[0] == zo.ZO_OK for o in out)

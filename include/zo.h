@@ -108,8 +108,10 @@ typedef struct {
  * with eps < ZO_BF16_EPS_MIN returns ZO_EINVAL. fp32 weights form
  * w +- eps z in fp32 (fused, one fp32 rounding) and run each fp32 product as
  * six bf16 products of the operands' three exact bf16 parts, accumulated in
- * fp32 (a non-finite weight gives non-finite losses); their two-stream form
- * exists for measurement only (central differences). */
+ * fp32. A weight that is not finite, or is 3.3961775e38 and more in size, gives
+ * NaN losses (also an infinite W_ih or W_hh, which would saturate its gate);
+ * of weights and activations below 2^-109 the lowest bits are lost. Their
+ * two-stream form exists for measurement only (central differences). */
 #define ZO_BF16_FUSED_EPS_MIN 0x1p-10f /* 9.765625e-4 */
 #define ZO_BF16_EPS_MIN 0x1p-17f       /* 7.62939453125e-6 */
 enum { ZO_PRODUCTS_AUTO = 0, ZO_PRODUCTS_FUSED = 1, ZO_PRODUCTS_SPLIT = 2 };

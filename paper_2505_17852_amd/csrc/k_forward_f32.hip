@@ -5,13 +5,16 @@
 // that. An fp32 value is the exact sum of three bf16 values (8 significant
 // bits each, the remainder of every rounding to nearest representable), so a
 // product of two fp32 operands a = a0 + a1 + a2, b = b0 + b1 + b2 is
-//     a0 b0 + (a0 b1 + a1 b0) + (a0 b2 + a1 b1 + a2 b0) + O(2^-27 a b):
+//     a0 b0 + (a0 b1 + a1 b0) + (a0 b2 + a1 b1 + a2 b0) + the rest:
 // six bf16 products, each exact in fp32, accumulated in fp32 smallest first.
-// The three terms left out are below the rounding of one fp32 product, and a
+// The three terms left out are 2^-27.5 of a b in the root mean square and at
+// most 2^-24.2 of it (one rounding of an fp32 product: 2^-25.2 and 2^-24), and a
 // sum of K products takes 6 K / 32 roundings instead of the K / 4 of
 // v_mfma_f32_16x16x4_f32. bf16 has fp32's exponent range, so nothing is
-// scaled. (An infinite weight or activation gives NaN: its remainder is
-// inf - inf.)
+// scaled; at its ends, an infinite weight or activation gives NaN (its remainder
+// is inf - inf), and so does a finite one from 0x7F7F8000 (3.3961775e38) on,
+// whose first part rounds to infinity, while the lowest parts of values below
+// 2^-109 flush.
 //
 // Operands.
 // - Activations (the perturbed embeddings x0 and the states h) are stored

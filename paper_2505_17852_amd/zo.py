@@ -159,8 +159,9 @@ def workspace_bytes_min(cfg, N: int, B: int, C_: int) -> int:
 
 
 def new_workspace(cfg, N: int, B: int, C_: int, device="cuda", probe_cache: bool = True) -> torch.Tensor:
-    """Device workspace for zo_perturbed_losses; probe_cache=False gives the
-    smallest one (normal probes then regenerated in every tile)."""
+    """Device workspace for zo_perturbed_losses, which also holds every call with
+    fewer probes, sequences or positions; probe_cache=False gives the smallest
+    one (probes then regenerated in every tile)."""
     n = workspace_bytes(cfg, N, B, C_) if probe_cache else workspace_bytes_min(cfg, N, B, C_)
     if n == 0:
         raise ValueError("invalid workspace request")

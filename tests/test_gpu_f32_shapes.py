@@ -83,6 +83,11 @@ def test_f32_shapes_agree(zo, L, H, N, B, probe):
             for n in (0, N // 2, N - 1):
                 s, t = f(cfg, theta, seed, eps, 1, td, i0=i0 + n)
                 assert torch.equal(s, a[n:n + 1]) and torch.equal(t, b if fd else b[n:n + 1])
+            if C == LENGTHS[0] and not fd:  # the two-stream form: the same products, other roundings
+                p = f(cfg, theta, seed, eps, N, td, i0=i0, products=zo.PRODUCTS_SPLIT)
+                q = f(cfg, theta, seed, eps, 1, td, i0=i0 + N - 1, products=zo.PRODUCTS_SPLIT)
+                for x, y, z in zip(p, q, (a, b)):
+                    assert torch.equal(y, x[N - 1:]) and torch.all((x - z).abs() <= RTOL * z.abs())
             if C == LENGTHS[0]:
                 kw = {} if fd else dict(as_double=True)
                 want = ref(cfg, oracle.init(cfg, 5), seed, eps, 1, tok, i0=i0 + N - 1, **kw)

@@ -505,13 +505,13 @@ inline WsPlan plan_for_bytes(const zo_config& c, const Rows& r, int32_t C, size_
   return w;
 }
 
-// Bytes that a call with N probes and B x C positions took before the fp32
-// states were stored in three parts: batches padded to 128 or 256 sequences with
-// bf16 weights, to 32 or 64 with fp32 ones, there also 4 bytes per activation,
-// chunks of kTimeChunk timesteps. It grows with N, B and C and does not
-// follow how the forward lays out its buffers; zo_perturbed_losses_noalloc holds
-// it against its fixed size, and the smallest fp32 workspace is at least as
-// large.
+// A fixed account of the bytes of a call with N probes and B x C positions:
+// batches padded to 128 or 256 sequences with bf16 weights, to 32 or 64 with
+// fp32 ones, 2 or 4 bytes per activation, chunks of kTimeChunk timesteps. It
+// grows with N, B and C and does not follow how the forward lays out its
+// buffers; zo_perturbed_losses_noalloc holds it against its fixed size (so the
+// shapes it takes stay the same), and the smallest fp32 workspace is at least
+// as large (fp32 states take 6 bytes, in fewer rows and timesteps).
 inline size_t account_bytes(const zo_config& c, int32_t N, int32_t B, int32_t C, bool fd) {
   const bool b16 = c.wdtype == ZO_WBF16;
   const int g = (b16 ? 128 : 32) * (fd ? 2 : 1);
@@ -532,9 +532,8 @@ inline size_t account_bytes(const zo_config& c, int32_t N, int32_t B, int32_t C,
 // the rows, the bound min(min(C, 64) steps, max(16 MiB, min(C, 8) steps)) of
 // time_chunk's bytes.
 //   full      every cache, except sign words or packed weights (fp32) beyond
-//             kExtraCap each: those had no share in the size when they were
-//             not stored, and a call that was close to the device's memory
-//             stays below it
+//             kExtraCap each: a call that fills the device's memory without
+//             them still fits, and takes them where a workspace has the room
 //   smallest  no caches beyond kSmallExtras of them and of longer chunks (a small
 //             model's smallest workspace then has what its full one has; 3
 //             layers of 160 units, 8 probes, a batch of 16: 668 us with the

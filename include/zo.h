@@ -240,7 +240,8 @@ int zo_update(const zo_config* cfg, void* theta, uint64_t seed, float eps, float
  * 16 + i when z_{i0+n}[32 w + 2 i + 1] = +1 (i < 16). zo_perturbed_losses writes it once per call and its
  * kernels read the words from it instead of regenerating them (the losses are
  * bit-identical either way); a smaller workspace regenerates them.
- * zo_probe_bits_offset returns 0 for shapes without the cache or invalid
+ * zo_probe_bits_offset returns 0 for shapes without the cache (models of 2^35
+ * parameters and more among them) or invalid
  * arguments. Host only. */
 size_t zo_probe_bits_offset(const zo_config* cfg, int32_t N, int32_t B, int32_t C);
 

@@ -325,8 +325,14 @@ inline bool bf16_matrices_fit(const zo_config& c) {
 // fp16 pair with one shift. The update can read the same words
 // (zo_update_cached) instead of regenerating them.
 // With fp32 weights the words are for the forward's own use; only the bf16
-// ones are offered to callers (bit_cache_kind).
-inline bool bit_cache_kind(const zo_config& c) { return c.probe == ZO_RADEMACHER && c.wdtype == ZO_WBF16; }
+// ones are offered to callers (bit_cache_kind). The bf16 kernels reach a probe's
+// words with 32-bit offsets too: from 2^35 parameters on they are regenerated.
+inline bool cacheable_probes(const zo_config& c) {
+  return c.probe != ZO_RADEMACHER || c.wdtype != ZO_WBF16 || make_layout(c).total < 1ull << 35;
+}
+inline bool bit_cache_kind(const zo_config& c) {
+  return c.probe == ZO_RADEMACHER && c.wdtype == ZO_WBF16 && cacheable_probes(c);
+}
 __host__ __device__ inline uint64_t bit_words(uint64_t P) { return (P + 127) / 128 * 4; }
 
 // A word of 32 flags with the even-indexed flags moved to bits 0..15 and the
@@ -490,9 +496,9 @@ inline WsPlan plan_for_bytes(const zo_config& c, const Rows& r, int32_t C, size_
     *used = k;
     return w.total <= ws_bytes;
   };
-  const bool pack = wpack_pays(c, C);
+  const bool pack = wpack_pays(c, C), probes = cacheable_probes(c);
   for (Caches k : {Caches{true, true}, Caches{true, false}, Caches{false, true}, Caches{false, false}}) {
-    if (k.wpack && !pack) continue;
+    if ((k.wpack && !pack) || (k.probes && !probes)) continue;
     if (!fits(mid, k)) continue;
     for (int T = most; T > mid; --T)
       if (fits(T, k)) return w;
@@ -547,7 +553,7 @@ inline WsSizes workspace_sizes(const zo_config& c, int32_t N, int32_t B, int32_t
   const Rows r = make_rows(N, B, size_granule(c, fd), fd);
   const int least = least_time_chunk(c, C);
   if (c.wdtype == ZO_WBF16)
-    return WsSizes{plan_workspace(c, r, least, Caches{true, false}).total,
+    return WsSizes{plan_workspace(c, r, least, Caches{cacheable_probes(c), false}).total,
                    plan_workspace(c, r, least, Caches{false, false}).total};
   // a plan without its chunk's buffers and with room for the zero state and each buffer's alignment
   const size_t step = chunk_step_bytes(c, r.M, vocab_tiles(c));

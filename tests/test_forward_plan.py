@@ -3,6 +3,7 @@ order), without a GPU: zo_api.hip and k_forward.hip built for the host with
 their kernel launchers replaced by checks (tests/helpers/forward_plan_driver.cpp).
 Every buffer of every launch lies inside the workspace and apart from the
 others, and no launch writes a state that its other workgroups still read."""
+import ctypes
 import math
 import os
 import random
@@ -209,3 +210,18 @@ def test_bf16_matrices_beyond_32_bit_offsets_are_refused(calls, zo):
         cfgs = [model(*s, wdtype, p) for s in shapes for p in (wl.RADEMACHER, wl.GAUSSIAN)]
         lines = [(c, fd, 1, 3, 2, zo.workspace_bytes(c, 1, 3, 2)) for c in cfgs for fd in (0, 1)]
         assert all(o[0] == want for o in calls(lines)), (shapes, wdtype)
+
+
+def test_sign_words_past_32_bit_offsets_are_not_cached(calls, zo):
+    """From 2^35 parameters on a probe's words take 4 GiB: the bf16 forward
+    regenerates them, whatever the workspace; below, a full one holds them."""
+    for L, cached in ((18, 1), (19, 0)):  # 33.1 and 35.0 G parameters; 2^35 is 34.4 G
+        cfg = model(L, 2000, 64, 15360, wl.BF16, wl.RADEMACHER)
+        assert (zo.param_count(cfg) < 1 << 35) == bool(cached)
+        full, small = zo.workspace_bytes(cfg, 1, 3, 2), zo.workspace_bytes_min(cfg, 1, 3, 2)
+        assert (full > small) == bool(cached)
+        offset = zo.lib().zo_probe_bits_offset(ctypes.byref(zo._cfg(cfg)), 1, 3, 2)
+        assert (offset > 0) == bool(cached)
+        for ws in (full, full + (8 << 30)):
+            (o,) = calls([(cfg, 0, 1, 3, 2, ws)])
+            assert o[0] == zo.ZO_OK and o[3] == cached, (L, ws, o)

@@ -434,7 +434,7 @@ inline size_t zero_state_bytes(const zo_config& c, int64_t M) {
   return (size_t)c.hidden * act_bytes(c) * (c.wdtype == ZO_WBF16 ? (size_t)M : 16);
 }
 
-inline int vocab_tiles(const zo_config& c) { return (c.vocab + vocab_tile(c) - 1) / vocab_tile(c); }
+inline int vocab_tiles(const zo_config& c) { return (int)(((int64_t)c.vocab + vocab_tile(c) - 1) / vocab_tile(c)); }
 inline size_t probe_cache_bytes(const zo_config& c, int32_t N) {
   if (c.probe == ZO_RADEMACHER) return (size_t)N * bit_words(make_layout(c).total) * 4;
   return (size_t)N * make_zcache_map(c).pg * (c.wdtype == ZO_WBF16 ? 2 * 2 : 4);
